@@ -116,6 +116,31 @@ template <int DT> __device__ __forceinline__ f32x4_t mfma16(const u32x4_t &a, co
 #endif
 }
 
+// c += a . b with the accumulator held in the accumulation registers by constraint: with 64 accumulator
+// blocks of four registers per lane the compiler otherwise keeps part of them in ordinary registers and
+// moves them back and forth in the loop.  The hazard between the last product and the first read of a sum
+// is the caller's: mfma_settle before the sums are used.  The operands must come from memory or LDS (an
+// ordinary vector instruction that writes one needs two wait states before the product reads it).
+template <int DT> __device__ __forceinline__ void mfma16_acc(const u32x4_t &a, const u32x4_t &b, f32x4_t &c) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  if constexpr (DT == DT_F16) asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
+  else asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
+#else
+  (void)a; (void)b; (void)c;
+#endif
+}
+template <int M, int N> __device__ __forceinline__ void mfma_settle(f32x4_t (&acc)[M][N]) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("s_nop 15\n\ts_nop 15");
+#pragma unroll
+  for (int i = 0; i < M; ++i)
+#pragma unroll
+    for (int j = 0; j < N; ++j) asm volatile("" : "+a"(acc[i][j]));
+#else
+  (void)acc;
+#endif
+}
+
 // The activation operand is read in 16-byte chunks of 8 columns.  Where the valid columns K of a row are
 // no multiple of 8 (the caller's rank-space rows of an upward projection alone), the chunk that holds
 // column K - 1 also holds columns that are not the kernel's to use (the weights there are zero, but

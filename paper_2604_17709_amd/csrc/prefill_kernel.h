@@ -163,19 +163,19 @@ __device__ __forceinline__ void prefill_body(const PfParams &P, const int bid, c
   const int kb0 = SPLIT ? kpart * P.kb_per_part : 0;          // first k-block of this workgroup
   const int tok0 = tb * BT;
 
-  constexpr int MB = MF / 2;                       // 32-feature blocks per wavefront
-  static_assert(MF == 8 || (MF == 4 && TB == 2 && !ROPE), "the hand-placed loop of the 256-token tile is written for four 32-feature blocks per wavefront");
-  f32x16_t acc[MB][TB];                            // [feature block][32-token block]
+  constexpr int TJ = 2 * TB;                       // 16-token blocks per wavefront (MF 16-feature blocks)
+  static_assert((MF == 8 || (MF == 4 && TB == 2 && !ROPE)) && (TB == 4 || TB == 2), "wavefront tiles the stage schedule is written for");
+  f32x4_t acc[MF][TJ];                             // [feature block][token block]
 #pragma unroll
-  for (int i = 0; i < MB; ++i)
+  for (int i = 0; i < MF; ++i)
 #pragma unroll
-    for (int j = 0; j < TB; ++j)
+    for (int j = 0; j < TJ; ++j)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+      for (int e = 0; e < 4; ++e) acc[i][j][e] = 0.f;
 
   // GLU: silu(gate product), rounded once to the storage type, kept in registers (as pairs) while the
-  // up product is accumulated: element [i][j][g] holds the four values of accumulator elements 4 g .. 4 g + 3
-  uint2 gpk[GLU ? MB : 1][GLU ? TB : 1][4];
+  // up product is accumulated: element [i][j] holds the four values of accumulator block (i, j)
+  uint2 gpk[GLU ? MF : 1][GLU ? TJ : 1];
   // One product of this workgroup's tile: acc += act . W^T over the whole k range of Q.  between() runs
   // once the first pipeline stages have been requested and before they are waited for.
   auto product = [&](const PfProblem &Q, auto &&between) {
@@ -245,160 +245,89 @@ __device__ __forceinline__ void prefill_body(const PfParams &P, const int bid, c
                                                  xrow[i] + kb, 0, 0, 0);
       }
     };
-    // Operand reads for the 32x32x16 product: lane l works on row (feature or token) l % 32 and on
-    // the 8 consecutive k of group 2 s + l / 32 of the stage's four k-groups, s = 0, 1 being the
-    // two k-steps of a stage.  In a packed 16-feature fragment that k-group of feature f % 16
-    // sits at lane position (f % 16) + 16 * group.
-    const int a_off = ((lane >> 4) & 1) * 64 + (lane & 15) + 16 * (lane >> 5);     // in uint4 units
-    const int b_row = wt * WTOK + (lane & 31);
-    const int b_swz = ((lane & 31) >> 2) & 3;
-    auto read_a = [&](int buf, int ib, int ks) -> u32x4_t {
-      return *reinterpret_cast<const u32x4_t *>(&S.w[buf][wf * MF + 2 * ib][0] + a_off + 32 * ks);
+    // Operand reads for the 16x16x32 product: lane l works on row (feature or token) l % 16 and on the 8
+    // consecutive k of group l / 16.  A packed 16-feature fragment is in that order already.
+    const int b_off = (wt * WTOK + (lane & 15)) * PF_XPITCH + (((lane >> 4) ^ ((lane >> 2) & 3)) * 16);
+    auto read_a = [&](int buf, int i) -> u32x4_t { return *reinterpret_cast<const u32x4_t *>(&S.w[buf][wf * MF + i][lane]); };
+    auto read_b = [&](int buf, int j) -> u32x4_t {
+      return *reinterpret_cast<const u32x4_t *>(&S.x[buf][b_off + 16 * j * PF_XPITCH]);
     };
-    auto read_b = [&](int buf, int jb, int ks) -> u32x4_t {
-      const int slot = (2 * ks + (lane >> 5)) ^ b_swz;
-      return *reinterpret_cast<const u32x4_t *>(&S.x[buf][(b_row + 32 * jb) * PF_XPITCH + slot * 16]);
-    };
-    constexpr int H1 = LPS / 2;            // loads 0 .. H1 - 1 of stage s + 3 go out during k-step 1 of stage s,
-                                           // loads H1 .. LPS - 1 during k-step 0 of stage s + 1: at most one
-                                           // load after each group of products, so their issue never holds
-                                           // the matrix pipeline up
-    static_assert(LPS - H1 <= 4 && H1 <= 4, "one load per token block and k-step");
-    if constexpr (TB == 4) {
+    constexpr int D = NST - 1;             // loads run D stages ahead of the products
+    constexpr int H1 = LPS / 2;            // loads 0 .. H1 - 1 of stage s + D go out in the second half of stage s,
+                                           // loads H1 .. LPS - 1 in the first half of stage s + 1
+    static_assert((D - 2) * LPS + H1 < 64, "the load counter has 6 bits");
+    // stages 0 .. D - 2 whole and the first half of stage D - 1, then wait for stage 0
 #pragma unroll
-      for (int i = 0; i < LPS; ++i) fetch_part(0, i);
-      if (n_stages > 1) {
+    for (int sg = 0; sg < D - 1; ++sg)
+      if (sg < n_stages) {
 #pragma unroll
-        for (int i = 0; i < LPS; ++i) fetch_part(1, i);
+        for (int i = 0; i < LPS; ++i) fetch_part(sg, i);
       }
-      if (n_stages > 2) {
+    if (D - 1 < n_stages) {
 #pragma unroll
-        for (int i = 0; i < H1; ++i) fetch_part(2, i);
-      }
-      between();
-      if (n_stages > 2) {
-        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LPS + H1) : "memory");
-      } else if (n_stages > 1) {
-        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LPS) : "memory");
-      } else {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      }
-    } else {
-      // stages 0 .. D - 2 whole and the first half of stage D - 1, then wait for stage 0
-      constexpr int D = NST - 1;
-      static_assert((D - 2) * LPS + H1 < 64, "the load counter has 6 bits");
-#pragma unroll
-      for (int sg = 0; sg < D - 1; ++sg)
-        if (sg < n_stages) {
-#pragma unroll
-          for (int i = 0; i < LPS; ++i) fetch_part(sg, i);
-        }
-      if (D - 1 < n_stages) {
-#pragma unroll
-        for (int i = 0; i < H1; ++i) fetch_part(D - 1, i);
-      }
-      between();
-      // outstanding at most: the stages after stage 0 (and the half stage D - 1)
-      if (D - 1 < n_stages) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((D - 2) * LPS + H1) : "memory");
-      else PfVmWait<0, D - 2, LPS, 0>::run(n_stages - 1);
+      for (int i = 0; i < H1; ++i) fetch_part(D - 1, i);
     }
+    between();
+    // outstanding at most: the stages after stage 0 (and the half stage D - 1)
+    if (D - 1 < n_stages) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((D - 2) * LPS + H1) : "memory");
+    else PfVmWait<0, D - 2, LPS, 0>::run(n_stages - 1);
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();          // stage 0 has landed everywhere
     asm volatile("" ::: "memory");
     if constexpr (TAIL) {
       if (st_fix == 0) fix_tail(0);
     }
-    // Operand reads run two groups of products ahead of their use (a group = the MB products that
-    // share one token operand, about 130 cycles): with the four wavefronts reading in step and the
-    // incoming tiles being written, one group of cover left the products waiting for LDS.
-    u32x4_t a0[MB], a1[MB], b[4];
+    // A stage is TJ groups of MF products that share one token operand (a group: 16 cycles per product).
+    // Token operands are read two groups ahead of their use into a ring of four, the feature operands of
+    // the next stage during the second half of this one.
+    u32x4_t a0[MF], a1[MF], b[4];
 #pragma unroll
-    for (int i = 0; i < MB; ++i) a0[i] = read_a(0, i, 0);
-    b[0] = read_b(0, 0, 0);
-    b[1] = read_b(0, 1, 0);
-    // (TB = 2: b[0..1] are the token operands of k-step 0, b[2..3] those of k-step 1)
-    // one stage; F2: the second half of stage st + 2 is still to be requested, F3: stage st + 3 exists
-    auto stage4 = [&](int st, auto f2, auto f3) {
-      constexpr bool F2 = decltype(f2)::value, F3 = decltype(f3)::value;
-      const int buf = st & (PF_STAGES - 1);
-      const int nbuf = (st + 1) & (PF_STAGES - 1);
-      // token operand of group g of this stage (g = 4 * k-step + token block); 8, 9 = next stage's 0, 1
-      auto read_bg = [&](int g) -> u32x4_t { return g < 8 ? read_b(buf, g & 3, g >> 2) : read_b(nbuf, g - 8, 0); };
-      // ---- k-step 0 of the stage; the feature operands of k-step 1 are read along the way.
-      // At most one memory instruction follows each product: its issue then hides behind the
-      // product's 32 cycles in the matrix pipeline (several in a row after a group held the next
-      // product up by about 40 cycles per group).
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-#pragma unroll
-        for (int i = 0; i < MB; ++i) {
-          acc[i][j] = mfma32<DT>(a0[i], b[j], acc[i][j]);
-          __builtin_amdgcn_sched_barrier(0);
-          if (F2 && i == 0 && H1 + j < LPS) fetch_part(st + 2, H1 + j);
-          if (i == 1 || MB == 1) b[(j + 2) & 3] = read_bg(j + 2);
-          if (i == 2 && j < 3 && (j == 0 ? 0 : j + 1) < MB) a1[j == 0 ? 0 : j + 1] = read_a(buf, j == 0 ? 0 : j + 1, 1);
-          if (i == 3 && j == 0 && MB > 1) a1[1] = read_a(buf, 1, 1);
-          __builtin_amdgcn_sched_barrier(0);
-        }
-      }
-      // ---- stage st + 1 has landed (this wavefront's part), barrier: it has landed everywhere and
-      // nobody reads the buffer of stage st - 1 any more, which is where stage st + 3 goes
-      if (F2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LPS) : "memory");
-      else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      // bare barrier: the wait above is the only ordering needed (loads into LDS are complete when
-      // the counter says so; the buffer about to be refilled was last read a whole k-step ago);
-      // the fence of __syncthreads() would drain every outstanding load instead
-      asm volatile("" ::: "memory");
-      __builtin_amdgcn_s_barrier();
-      asm volatile("" ::: "memory");
-      // (the chunk that holds column K - 1 is in the last stage: only the stages that run without further
-      // requests can precede it, so the steady-state loop carries no branch for this)
-      if constexpr (TAIL && !F2 && !F3) {
-        if (st + 1 == st_fix) fix_tail(nbuf);           // (uniform)
-      }
-      // ---- k-step 1; the operands of the next stage's k-step 0 are read along the way
-      // (after the last stage these read a stage buffer nobody writes any more; the values are unused)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-#pragma unroll
-        for (int i = 0; i < MB; ++i) {
-          acc[i][j] = mfma32<DT>(a1[i], b[j], acc[i][j]);
-          __builtin_amdgcn_sched_barrier(0);
-          if (F3 && i == 0 && j < H1) fetch_part(st + 3, j);
-          if (i == 1 || MB == 1) b[(j + 2) & 3] = read_bg(j + 6);
-          // a0 is not in use during k-step 1
-          if (i == 2 && j < 3 && (j == 0 ? 0 : j + 1) < MB) a0[j == 0 ? 0 : j + 1] = read_a(nbuf, j == 0 ? 0 : j + 1, 0);
-          if (i == 3 && j == 0 && MB > 1) a0[1] = read_a(nbuf, 1, 0);
-          __builtin_amdgcn_sched_barrier(0);
-        }
-      }
-    };
-    // TB = 2: the operands of a whole k-step are read while the previous one is multiplied
-    // (MB + TB reads and up to H1 load requests over the MB * TB products of a k-step); loads run
-    // D = NST - 1 stages ahead.  STEADY: stage st + D exists (no conditions in the loop body).
-    auto stage2 = [&](int st, auto steady) {
+    for (int i = 0; i < MF; ++i) a0[i] = read_a(0, i);
+    b[0] = read_b(0, 0);
+    b[1] = read_b(0, 1);
+    // One stage: feature operands in `a`, those of the next stage into `an`.  STEADY: stage st + D exists
+    // (no conditions in the loop body).  At most two memory instructions follow a product: their issue
+    // hides behind the products' cycles in the matrix pipeline.
+    auto stage = [&](int st, u32x4_t (&a)[MF], u32x4_t (&an)[MF], auto steady) {
       constexpr bool STEADY = decltype(steady)::value;
-      constexpr int D = NST - 1;
       const int buf = st % NST;
       const int nbuf = (st + 1) % NST;
-      const bool i2 = STEADY || st + D - 1 < n_stages;     // second half of stage st + D - 1 still to request
+      const bool i2 = STEADY || st + D - 1 < n_stages;     // second part of stage st + D - 1 still to request
       const bool i3 = STEADY || st + D < n_stages;         // stage st + D exists
-      constexpr int NS = MB * TB;                          // products = slots of a k-step
-      static_assert(TB == 4 || (MB + TB <= NS && LPS - H1 <= NS && H1 <= NS), "slots of a k-step");
+      constexpr int HG = TJ / 2, HN = HG * MF;             // groups / products of half a stage
+      constexpr int AN = MF / HG;                          // next-stage feature operands read per group of the second half
+      auto half = [&](auto second) {
+        constexpr bool SECOND = decltype(second)::value;
+        constexpr int NL = SECOND ? H1 : LPS - H1;         // load requests of this half
 #pragma unroll
-      for (int j = 0; j < TB; ++j) {
+        for (int gg = 0; gg < HG; ++gg) {
+          const int g = gg + (SECOND ? HG : 0);
 #pragma unroll
-        for (int i = 0; i < MB; ++i) {
-          const int slot = j * MB + i;
-          acc[i][j] = mfma32<DT>(a0[i], b[j], acc[i][j]);
-          __builtin_amdgcn_sched_barrier(0);
-          if (slot < MB) a1[slot] = read_a(buf, slot, 1);
-          else if (slot - MB < TB) b[2 + slot - MB] = read_b(buf, slot - MB, 1);
-          if (slot >= NS - (LPS - H1) && i2) fetch_part(st + D - 1, H1 + slot - (NS - (LPS - H1)));
-          __builtin_amdgcn_sched_barrier(0);
+          for (int i = 0; i < MF; ++i) {
+            const int n = gg * MF + i;
+            mfma16_acc<DT>(a[i], b[g & 3], acc[i][g]);
+#pragma unroll
+            for (int l = 0; l < NL; ++l)
+              if (l * HN / NL == n) {
+                if (SECOND) { if (i3) fetch_part(st + D, l); }
+                else if (i2) fetch_part(st + D - 1, H1 + l);
+              }
+            if (i == 1) b[(g + 2) & 3] = g + 2 < TJ ? read_b(buf, g + 2) : read_b(nbuf, g + 2 - TJ);
+            if (SECOND) {
+#pragma unroll
+              for (int t = 0; t < AN; ++t)
+                if (i == 2 + t * (MF - 2) / AN) an[gg * AN + t] = read_a(nbuf, gg * AN + t);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+          }
         }
-      }
-      // stage st + 1 has landed once at most the loads of the stages st + 2 .. st + D - 1 are outstanding
+      };
+      half(std::false_type{});
+      // stage st + 1 has landed (this wavefront's part) once at most the loads of the stages st + 2 .. st + D - 1
+      // are outstanding; after the barrier it has landed everywhere and nobody reads the buffer of stage st - 1
+      // any more, which is where stage st + D goes.  A bare barrier: the wait is the only ordering needed
+      // (loads into LDS are complete when the counter says so); the fence of __syncthreads() would drain
+      // every outstanding load instead.
       if (STEADY) {
         asm volatile("s_waitcnt vmcnt(%0)" ::"n"((D - 2) * LPS) : "memory");
       } else {
@@ -407,38 +336,31 @@ __device__ __forceinline__ void prefill_body(const PfParams &P, const int bid, c
         PfVmWait<0, D - 2, LPS, 0>::run(rem);
       }
       asm volatile("" ::: "memory");
-      __builtin_amdgcn_s_barrier();          // ... everywhere, and nobody reads the buffer of stage st - 1 any more
+      __builtin_amdgcn_s_barrier();
       asm volatile("" ::: "memory");
+      // (the chunk that holds column K - 1 is in the last stage: only stages without a whole pipeline behind
+      // them can precede it, so the steady-state loop carries no branch for this)
       if constexpr (TAIL && !STEADY) {
-        if (st + 1 == st_fix) fix_tail(nbuf);
+        if (st + 1 == st_fix) fix_tail(nbuf);              // (uniform)
       }
-#pragma unroll
-      for (int j = 0; j < TB; ++j) {
-#pragma unroll
-        for (int i = 0; i < MB; ++i) {
-          const int slot = j * MB + i;
-          acc[i][j] = mfma32<DT>(a1[i], b[2 + j], acc[i][j]);
-          __builtin_amdgcn_sched_barrier(0);
-          if (slot < MB) a0[slot] = read_a(nbuf, slot, 0);
-          else if (slot - MB < TB) b[slot - MB] = read_b(nbuf, slot - MB, 0);
-          if (slot >= NS - H1 && i3) fetch_part(st + D, slot - (NS - H1));
-          __builtin_amdgcn_sched_barrier(0);
-        }
-      }
+      // (after the last stage the reads ahead hit a stage buffer nobody writes any more; the values are unused)
+      half(std::true_type{});
     };
     {
       const std::true_type yes;
       const std::false_type no;
       int st = 0;
-      if constexpr (TB == 4) {
-        for (; st + 3 < n_stages; ++st) stage4(st, yes, yes);
-        if (st + 2 < n_stages) { stage4(st, yes, no); ++st; }
-        for (; st < n_stages; ++st) stage4(st, no, no);
-      } else {
-        for (; st + NST - 1 < n_stages; ++st) stage2(st, yes);
-        for (; st < n_stages; ++st) stage2(st, no);
+      for (; st + 1 + D < n_stages; st += 2) {
+        stage(st, a0, a1, yes);
+        stage(st + 1, a1, a0, yes);
+      }
+      for (; st < n_stages; st += 2) {
+        stage(st, a0, a1, no);
+        if (st + 1 >= n_stages) break;
+        stage(st + 1, a1, a0, no);
       }
     }
+    mfma_settle(acc);
   };
   if constexpr (GLU) {
     // Both products of the tile in this workgroup (Sec. 4.1: gate and up share x and the output
@@ -449,26 +371,24 @@ __device__ __forceinline__ void prefill_body(const PfParams &P, const int bid, c
     product(P.prob[1], [&] {
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int i = 0; i < MB; ++i)
+      for (int i = 0; i < MF; ++i)
 #pragma unroll
-        for (int j = 0; j < TB; ++j)
+        for (int j = 0; j < TJ; ++j) {
+          // (the sums are taken out of the accumulator registers here, by hand: the compiler would
+          // move all 256 of them to ordinary registers at the end of the gate product's loop, where
+          // they would have to live through the requests above)
+          float z[4];
 #pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            // (the sums are taken out of the accumulator registers here, by hand: the compiler would
-            // move all 256 of them to ordinary registers at the end of the gate product's loop, where
-            // they would have to live through the requests above)
-            float z[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(z[e]) : "a"(acc[i][j][4 * g + e]));
-              acc[i][j][4 * g + e] = 0.f;
-            }
-            gpk[i][j][g].x = pack2<DT>(silu_f32(z[0]), silu_f32(z[1]));
-            gpk[i][j][g].y = pack2<DT>(silu_f32(z[2]), silu_f32(z[3]));
-            // (the packed values are made opaque here: otherwise the compiler defers silu to the
-            // epilogue and keeps all 256 raw gate sums alive through the second product's loop)
-            asm volatile("" : "+v"(gpk[i][j][g].x), "+v"(gpk[i][j][g].y));
+          for (int e = 0; e < 4; ++e) {
+            asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(z[e]) : "a"(acc[i][j][e]));
+            acc[i][j][e] = 0.f;
           }
+          gpk[i][j].x = pack2<DT>(silu_f32(z[0]), silu_f32(z[1]));
+          gpk[i][j].y = pack2<DT>(silu_f32(z[2]), silu_f32(z[3]));
+          // (the packed values are made opaque here: otherwise the compiler defers silu to the
+          // epilogue and keeps all 256 raw gate sums alive through the second product's loop)
+          asm volatile("" : "+v"(gpk[i][j].x), "+v"(gpk[i][j].y));
+        }
     });
   } else {
     product(P.prob[pi], [] {});
@@ -479,48 +399,41 @@ __device__ __forceinline__ void prefill_body(const PfParams &P, const int bid, c
   asm volatile("" : "+v"(tid_e));
   const int lane_e = tid_e & 63, wave_e = tid_e >> 6, wf_e = wave_e & 1, wt_e = wave_e >> 1;
   if constexpr (SPLIT) {
-    // element 4 g + e of block (i, j) is feature 32 i + 8 g + 4 (lane / 32) + e, token 32 j + lane % 32:
-    // four consecutive features = one 16-byte store; the buffer has whole tiles, no bounds to check
+    // element e of block (i, j) is feature 16 i + 4 (lane / 16) + e, token 16 j + lane % 16: four
+    // consecutive features = one 16-byte store; the buffer has whole tiles, no bounds to check
     const long long F = (long long)P.n_fblocks * (32 * MF);
-    float *dst = P.part + (long long)kpart * P.part_stride + (long long)(tok0 + wt_e * 128 + (lane_e & 31)) * F +
-                 (fb * BF_TILES + wf_e * MF) * 16 + 4 * (lane_e >> 5);
+    float *dst = P.part + (long long)kpart * P.part_stride + (long long)(tok0 + wt_e * WTOK + (lane_e & 15)) * F +
+                 (fb * BF_TILES + wf_e * MF) * 16 + 4 * (lane_e >> 4);
 #pragma unroll
-    for (int i = 0; i < MB; ++i)
+    for (int i = 0; i < MF; ++i)
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const f32x4_t v = {acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
-          *reinterpret_cast<f32x4_t *>(dst + (long long)(32 * j) * F + 32 * i + 8 * g) = v;
-        }
+      for (int j = 0; j < TJ; ++j) *reinterpret_cast<f32x4_t *>(dst + (long long)(16 * j) * F + 16 * i) = acc[i][j];
     return;
   }
   // accumulators -> bf16 pairs first (registers only): it overlaps the wait for the slowest wavefront.
   // (GLU: not ahead of the barrier: 128 registers of pairs beside the 128 of the gate values would not
   // fit; every pair is formed right before it is written to LDS instead)
-  uint2 pk[GLU ? 1 : MB][GLU ? 1 : TB][4];
+  uint2 pk[GLU ? 1 : MF][GLU ? 1 : TJ];
   if constexpr (!GLU) {
 #pragma unroll
-  for (int i = 0; i < MB; ++i)
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
+    for (int i = 0; i < MF; ++i) {
       float b[4] = {0.f, 0.f, 0.f, 0.f};
       if (POST && Q.bias != nullptr) {
-        // element 4 g + e of block (i, j) is feature 32 i + 8 g + 4 (lane / 32) + e of this wavefront's 16 MF features
-        const int f0 = (fb * BF_TILES + wf_e * MF) * 16 + 32 * i + 8 * g + 4 * (lane_e >> 5);
+        // element e of block (i, j) is feature 16 i + 4 (lane / 16) + e of this wavefront's 16 MF features
+        const int f0 = (fb * BF_TILES + wf_e * MF) * 16 + 16 * i + 4 * (lane_e >> 4);
 #pragma unroll
         for (int e = 0; e < 4; ++e)
           if (f0 + e < Q.width) b[e] = cvt_in<DT>(Q.bias[f0 + e]);
       }
 #pragma unroll
-      for (int j = 0; j < TB; ++j) {
-        float v[4] = {acc[i][j][4 * g + 0], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
+      for (int j = 0; j < TJ; ++j) {
+        float v[4] = {acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]};
         if (POST) {
 #pragma unroll
           for (int e = 0; e < 4; ++e) v[e] = act_f32(v[e] + b[e], Q.post_act);
         }
-        pk[GLU ? 0 : i][GLU ? 0 : j][g].x = pack2<DT>(v[0], v[1]);
-        pk[GLU ? 0 : i][GLU ? 0 : j][g].y = pack2<DT>(v[2], v[3]);
+        pk[GLU ? 0 : i][GLU ? 0 : j].x = pack2<DT>(v[0], v[1]);
+        pk[GLU ? 0 : i][GLU ? 0 : j].y = pack2<DT>(v[2], v[3]);
       }
     }
   }
@@ -528,17 +441,17 @@ __device__ __forceinline__ void prefill_body(const PfParams &P, const int bid, c
   // ---- epilogue: through LDS (free once the barrier below has passed), so that the global
   // stores are 16 bytes per lane and whole contiguous rows per group of lanes (storing straight
   // from the accumulator arrangement, 32 bytes per row and instruction, measured slower).
-  // Accumulator element 4 g + e of block (i, j) is feature 32 i + 8 g + 4 (l / 32) + e of token
-  // 32 j + l % 32.  Each wavefront keeps its tile [128 tokens][16 MF features] as bf16 in its own
-  // LDS region: rows of CPR 16-byte chunks (8 features each), chunk position XORed with the row
-  // number, the two 8-byte halves of a chunk swapped in rows with bit 3 set (16 consecutive rows
-  // of one 8-byte write then cover 128 bytes of distinct banks).  Only the wavefront itself
-  // touches the region: no barrier.
+  // Accumulator element e of block (i, j) is feature 16 i + 4 (l / 16) + e of token 16 j + l % 16.  Each
+  // wavefront keeps its tile [WTOK tokens][16 MF features] in its own LDS region: rows of CPR 16-byte
+  // chunks (8 features each), chunk position XORed with the row (16 rows at one logical chunk then cover
+  // all banks, see eswz).  Only the wavefront itself touches the region: no barrier.
   constexpr int CPR = 2 * MF;                      // chunks per row
   constexpr int PITCH = CPR * 16;
   constexpr int RPI = 64 / CPR;                    // token rows per store instruction
   static_assert(4 * WTOK * PITCH <= (int)sizeof(PfShared<MF, TB>), "epilogue tile fits the stage buffers");
   unsigned char *E = smem_raw + wave_e * (WTOK * PITCH);
+  // (256-byte rows span all banks; 128-byte rows half of them, the row's parity picks the half)
+  auto eswz = [](int row) { return CPR == 16 ? (row & 15) : ((row >> 1) & (CPR - 1)); };
   // this lane's chunk: 8 consecutive features
   const int c = lane_e & (CPR - 1), rsub = lane_e / CPR;
   uint16_t *const out = Q.out;
@@ -572,30 +485,28 @@ __device__ __forceinline__ void prefill_body(const PfParams &P, const int bid, c
   load_tab(0);
   __syncthreads();         // the epilogue reuses the LDS buffers (the loads above are in flight meanwhile)
   {
-    const int wrow = lane_e & 31, wswz = lane_e & (CPR - 1);
-    const int whalf = ((lane_e >> 5) ^ ((lane_e >> 3) & 1)) * 8;
+    const int wrow = lane_e & 15, wchunk = lane_e >> 5, whalf = ((lane_e >> 4) & 1) * 8;
 #pragma unroll
-    for (int i = 0; i < MB; ++i)
+    for (int i = 0; i < MF; ++i)
 #pragma unroll
-      for (int j = 0; j < TB; ++j)
+      for (int j = 0; j < TJ; ++j) {
+        uint2 w;
+        if constexpr (GLU) {     // h = silu(gate) * up in fp32, one rounding of the result
+          const uint2 sg = gpk[GLU ? i : 0][GLU ? j : 0];
+          float u[4];            // (read out of the accumulator registers one by one, see the gate product above)
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          uint2 w;
-          if constexpr (GLU) {     // h = silu(gate) * up in fp32, one rounding of the result
-            const uint2 sg = gpk[GLU ? i : 0][GLU ? j : 0][g];
-            float u[4];            // (read out of the accumulator registers one by one, see the gate product above)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(u[e]) : "a"(acc[i][j][4 * g + e]));
-            w.x = pack2<DT>(u[0] * lo_f32<DT>(sg.x), u[1] * hi_f32<DT>(sg.x));
-            w.y = pack2<DT>(u[2] * lo_f32<DT>(sg.y), u[3] * hi_f32<DT>(sg.y));
-          } else {
-            w = pk[GLU ? 0 : i][GLU ? 0 : j][g];
-          }
-          *reinterpret_cast<uint2 *>(E + (32 * j + wrow) * PITCH + (((4 * i + g) ^ wswz) * 16) + whalf) = w;
-          // (one pair at a time, in source order: scheduled freely, all 256 sums are read out of the
-          // accumulator registers first, which does not fit beside the gate values)
-          if constexpr (GLU) __builtin_amdgcn_sched_barrier(0);
+          for (int e = 0; e < 4; ++e) asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(u[e]) : "a"(acc[i][j][e]));
+          w.x = pack2<DT>(u[0] * lo_f32<DT>(sg.x), u[1] * hi_f32<DT>(sg.x));
+          w.y = pack2<DT>(u[2] * lo_f32<DT>(sg.y), u[3] * hi_f32<DT>(sg.y));
+        } else {
+          w = pk[GLU ? 0 : i][GLU ? 0 : j];
         }
+        // (the swizzle of row 16 j + wrow is that of wrow)
+        *reinterpret_cast<uint2 *>(E + (16 * j + wrow) * PITCH + (((2 * i + wchunk) ^ eswz(wrow)) * 16) + whalf) = w;
+        // (one pair at a time, in source order: scheduled freely, all 256 sums are read out of the
+        // accumulator registers first, which does not fit beside the gate values)
+        if constexpr (GLU) __builtin_amdgcn_sched_barrier(0);
+      }
   }
   if (ROPE && NBATCH > 1) load_tab(1);
   // LDS reads of the next batch are issued before the stores of this one (different units)
@@ -604,14 +515,13 @@ __device__ __forceinline__ void prefill_body(const PfParams &P, const int bid, c
 #pragma unroll
     for (int qq = 0; qq < BQ; ++qq) {
       const int row = (bt * BQ + qq) * RPI + rsub;
-      dd[qq] = *reinterpret_cast<const u32x4_t *>(E + row * PITCH + ((c ^ (row & (CPR - 1))) * 16));
+      dd[qq] = *reinterpret_cast<const u32x4_t *>(E + row * PITCH + ((c ^ eswz(row)) * 16));
     }
   };
   auto store_batch = [&](int bt, u32x4_t (&dd)[BQ]) {
 #pragma unroll
     for (int qq = 0; qq < BQ; ++qq) {
       const int q = bt * BQ + qq;
-      if (((q * RPI) >> 3) & 1) dd[qq] = u32x4_t{dd[qq][2], dd[qq][3], dd[qq][0], dd[qq][1]};
       if constexpr (ROPE) {
         // This lane's chunk c holds features 8 (c % 8) .. + 7 of the first (c < 8) or the second half
         // of a head, the lane 8 further round its row of 16 lanes holds the other element of each pair
@@ -648,8 +558,7 @@ __device__ __forceinline__ void prefill_body(const PfParams &P, const int bid, c
     for (int q = 0; q < NQ; ++q) {
       if (tok_base + q * RPI >= P.T) break;
       const int row = q * RPI + rsub;
-      u32x4_t d = *reinterpret_cast<const u32x4_t *>(E + row * PITCH + ((c ^ (row & (CPR - 1))) * 16));
-      if (((q * RPI) >> 3) & 1) d = u32x4_t{d[2], d[3], d[0], d[1]};
+      const u32x4_t d = *reinterpret_cast<const u32x4_t *>(E + row * PITCH + ((c ^ eswz(row)) * 16));
       uint16_t *o = dst + (long long)(q * RPI) * ldo;
       for (int e = 0; e < 8; ++e) {
         if (col + e >= width) break;
