@@ -11,6 +11,7 @@
 #include <cstring>
 #include <atomic>
 #include <mutex>
+#include <type_traits>
 
 #include "common.h"
 #include "decode_kernel.h"
@@ -436,6 +437,56 @@ int run_decode(const Group &gq) {
                                       : launch_decode_nt<DT_BF16, 1>(P, gq.glu, grid2, gq.stream, gq.down_only);
 }
 
+// ---- RAW layout: one product of a call (raw_gemm_kernel in generic_kernels.h)
+template <typename TA, typename TB, typename TC, bool DUAL> struct RawCall {
+  RawOperands<TA, TB> p, p2;               // (p2: DUAL only)
+  TC *C; int64_t ldc;
+  int64_t M, N;
+  const TC *bias; int act;
+};
+template <int MB, int NV, int NW, typename TA, typename TB, typename TC, bool DUAL>
+void launch_raw(const RawCall<TA, TB, TC, DUAL> &c, hipStream_t s) {
+  const int64_t mt = ceil_div(c.M, 16 * MB), nt = ceil_div(c.N, 16 * NV);
+  constexpr int64_t SLICE = 32768;         // (a launch is limited to 65535 workgroups along y and z)
+  hipLaunchKernelGGL((raw_gemm_kernel<TA, TB, TC, DUAL, MB, NV, NW>), dim3((unsigned)mt, (unsigned)(nt < SLICE ? nt : SLICE), (unsigned)ceil_div(nt, SLICE)),
+                     dim3(64 * NW), 0, s, c.p, c.p2, c.C, c.ldc, (int)c.M, (int)c.N, c.bias, c.act);
+}
+// Tile of a product: the one with the smallest estimate  rounds of workgroups x time of one workgroup.  The
+// times (per k, relative) are those of the tiles in a launch that fills the device, 2048 x 1024 x 1024 in fp32:
+// 64 x 64 45.9 us, 32 x 64 45.4, 64 x 32 51.7, 32 x 32 65.6, 16 x 32 68, 16 x 16 88 us.  They predicted the fastest
+// or a tile within 10 % of it for 201 x 1638 x 4096 (64 x 32: 48 us, 64 x 64: 71), 201 x 4096 x 1638 (64 x 64: 32 us,
+// 16 x 16: 65), 64 x 4096 x 1638, 100 x 1000 x 300, 512 x 819 x 4096, 2048 x 300 x 700 and 1000 x 64 x 64.
+// Tiles of 64 columns read four elements of a B row at once and need those rows aligned to the four (a row
+// pitch of 819 fp32 elements: 77 us for 512 x 819 x 4096 as 32 x 64 tiles against 49 as 64 x 32).
+template <typename TA, typename TB, typename TC, bool DUAL>
+int run_raw(const RawCall<TA, TB, TC, DUAL> &c, hipStream_t s, const char *what) {
+  const int cus = device_cus();
+  if (cus <= 0) return fail(DEINFER_ERR_DEVICE, "no usable HIP device");
+  auto rows4 = [](const RawOperands<TA, TB> &p) { return aligned(p.B, 4 * sizeof(TB)) && p.ldb % 4 == 0; };
+  const bool wide = rows4(c.p) && (!DUAL || rows4(c.p2));
+  struct Tile { int mb, nv; double cost; };
+  static constexpr Tile tiles[] = {{4, 4, 0.172}, {2, 4, 0.085}, {4, 2, 0.097}, {2, 2, 0.0615}, {1, 2, 0.032}, {1, 1, 0.0205}};
+  int best = -1;
+  double best_cost = 0;
+  for (int i = 0; i < 6; ++i) {
+    if (tiles[i].nv == 4 && (!wide || DUAL)) continue;      // (two products: their sums would not leave room for those)
+    const double cost = (double)ceil_div(ceil_div(c.M, 16 * tiles[i].mb) * ceil_div(c.N, 16 * tiles[i].nv), (int64_t)cus) * tiles[i].cost;
+    if (best < 0 || cost < best_cost) { best = i; best_cost = cost; }
+  }
+  // few tiles and a long k: 16 wavefronts share the k range of a tile instead of four
+  const int64_t wgs = ceil_div(c.M, 16) * ceil_div(c.N, 16);
+  if (best == 5 && 4 * wgs <= cus && c.p.K >= 512) launch_raw<1, 1, 16>(c, s);
+  else if (best == 5) launch_raw<1, 1, 4>(c, s);
+  else if (best == 4) launch_raw<1, 2, 4>(c, s);
+  else if (best == 3) launch_raw<2, 2, 4>(c, s);
+  else if (best == 2) launch_raw<4, 2, 4>(c, s);
+  if constexpr (!DUAL) {
+    if (best == 1) launch_raw<2, 4, 4>(c, s);
+    else if (best == 0) launch_raw<4, 4, 4>(c, s);
+  }
+  return check_launch(what);
+}
+
 template <typename TE>
 int run_generic(const Group &gq) {
   const int64_t T = gq.T;
@@ -447,34 +498,24 @@ int run_generic(const Group &gq) {
   int64_t off[3] = {0, 0, 0};
   int64_t acc = 0;
   for (int i = 0; i < gq.n; ++i) { off[i] = acc; acc += gq.f[i]->r; }
-  if (gq.up_only && gq.glu) {
-    const deinfer_factors_t *fg = gq.f[0], *fu = gq.f[1];
-    dim3 grid((unsigned)ceil_div(fg->d_out, GT), (unsigned)ceil_div(T, GT));
-    hipLaunchKernelGGL((gemm_generic_kernel<TE, TE, TE, true>), grid, dim3(GTHREADS), 0, gq.stream,
-                       x, gq.ldx, static_cast<const TE *>(fg->V), fg->ldv, (int)fg->r,
-                       static_cast<const TE *>(gq.x2), gq.ldx2, static_cast<const TE *>(fu->V), fu->ldv, (int)fu->r,
-                       static_cast<TE *>(gq.out[0]), gq.ldo[0], (int)T, (int)fg->d_out);
-    return check_launch("generic GLU upward projection");
-  }
+  // second stages: V of pair i as the B operand, `t` with pitch `ld` as the A operand
+  auto up = [&](int i, auto *t, int64_t ld) {
+    return RawOperands<std::remove_cv_t<std::remove_pointer_t<decltype(t)>>, TE>{t, ld, static_cast<const TE *>(gq.f[i]->V), gq.f[i]->ldv, (int)gq.f[i]->r};
+  };
   if (gq.up_only) {
     // the caller's rank-space rows are the activation operand of the upward projection
-    const deinfer_factors_t *f = gq.f[0];
-    dim3 grid((unsigned)ceil_div(f->d_out, GT), (unsigned)ceil_div(T, GT));
-    hipLaunchKernelGGL((gemm_generic_kernel<TE, TE, TE, false>), grid, dim3(GTHREADS), 0, gq.stream,
-                       x, gq.ldx, static_cast<const TE *>(f->V), f->ldv, (int)f->r,
-                       (const TE *)nullptr, (int64_t)0, (const TE *)nullptr, (int64_t)0, 0,
-                       static_cast<TE *>(gq.out[0]), gq.ldo[0], (int)T, (int)f->d_out);
-    return check_launch("generic upward projection");
+    if (gq.glu)
+      return run_raw(RawCall<TE, TE, TE, true>{up(0, x, gq.ldx), up(1, static_cast<const TE *>(gq.x2), gq.ldx2),
+                                               static_cast<TE *>(gq.out[0]), gq.ldo[0], T, gq.f[0]->d_out, nullptr, ACT_NONE},
+                     gq.stream, "generic GLU upward projection");
+    return run_raw(RawCall<TE, TE, TE, false>{up(0, x, gq.ldx), {}, static_cast<TE *>(gq.out[0]), gq.ldo[0], T, gq.f[0]->d_out, nullptr, ACT_NONE},
+                   gq.stream, "generic upward projection");
   }
   // stage 1: t[:, off_i : off_i + r_i] = x . U_i   (downward projections, Sec. 4.1)
   for (int i = 0; i < gq.n; ++i) {
     const deinfer_factors_t *f = gq.f[i];
-    dim3 grid((unsigned)ceil_div(f->r, GT), (unsigned)ceil_div(T, GT));
-    hipLaunchKernelGGL((gemm_generic_kernel<TE, TE, float, false>), grid, dim3(GTHREADS), 0, gq.stream,
-                       x, gq.ldx, static_cast<const TE *>(f->U), f->ldu, (int)f->d_in,
-                       (const TE *)nullptr, (int64_t)0, (const TE *)nullptr, (int64_t)0, 0,
-                       t32 + off[i], ldt, (int)T, (int)f->r);
-    if (int rc = check_launch("generic stage 1")) return rc;
+    if (int rc = run_raw(RawCall<TE, TE, float, false>{{x, gq.ldx, static_cast<const TE *>(f->U), f->ldu, (int)f->d_in}, {},
+                                                       t32 + off[i], ldt, T, f->r, nullptr, ACT_NONE}, gq.stream, "generic stage 1")) return rc;
     if (gq.t_out[i]) {
       const int64_t cnt = T * f->r;
       hipLaunchKernelGGL((copy2d_kernel<float, TE>), dim3((unsigned)ceil_div(cnt, 256)), dim3(256), 0, gq.stream,
@@ -484,25 +525,14 @@ int run_generic(const Group &gq) {
   }
   if (gq.down_only) return DEINFER_OK;
   // stage 2: upward projections
-  if (gq.glu) {
-    const deinfer_factors_t *fg = gq.f[0], *fu = gq.f[1];
-    dim3 grid((unsigned)ceil_div(fg->d_out, GT), (unsigned)ceil_div(T, GT));
-    hipLaunchKernelGGL((gemm_generic_kernel<float, TE, TE, true>), grid, dim3(GTHREADS), 0, gq.stream,
-                       t32 + off[0], ldt, static_cast<const TE *>(fg->V), fg->ldv, (int)fg->r,
-                       t32 + off[1], ldt, static_cast<const TE *>(fu->V), fu->ldv, (int)fu->r,
-                       static_cast<TE *>(gq.out[0]), gq.ldo[0], (int)T, (int)fg->d_out);
-    return check_launch("generic GLU stage 2");
-  }
-  for (int i = 0; i < gq.n; ++i) {
-    const deinfer_factors_t *f = gq.f[i];
-    dim3 grid((unsigned)ceil_div(f->d_out, GT), (unsigned)ceil_div(T, GT));
-    hipLaunchKernelGGL((gemm_generic_kernel<float, TE, TE, false>), grid, dim3(GTHREADS), 0, gq.stream,
-                       t32 + off[i], ldt, static_cast<const TE *>(f->V), f->ldv, (int)f->r,
-                       (const float *)nullptr, (int64_t)0, (const TE *)nullptr, (int64_t)0, 0,
-                       static_cast<TE *>(gq.out[i]), gq.ldo[i], (int)T, (int)f->d_out,
-                       static_cast<const TE *>(gq.bias), gq.act);
-    if (int rc = check_launch("generic stage 2")) return rc;
-  }
+  const float *t = t32;
+  if (gq.glu)
+    return run_raw(RawCall<float, TE, TE, true>{up(0, t + off[0], ldt), up(1, t + off[1], ldt),
+                                                static_cast<TE *>(gq.out[0]), gq.ldo[0], T, gq.f[0]->d_out, nullptr, ACT_NONE},
+                   gq.stream, "generic GLU stage 2");
+  for (int i = 0; i < gq.n; ++i)
+    if (int rc = run_raw(RawCall<float, TE, TE, false>{up(i, t + off[i], ldt), {}, static_cast<TE *>(gq.out[i]), gq.ldo[i], T, gq.f[i]->d_out,
+                                                       static_cast<const TE *>(gq.bias), gq.act}, gq.stream, "generic stage 2")) return rc;
   return DEINFER_OK;
 }
 

@@ -1,87 +1,236 @@
-// Generic (any size, any alignment) kernels for RAW-layout factor pairs, fp32 or bf16
-// storage with fp32 accumulation.  Plain LDS-tiled FMA GEMM on row-major operands:
+// Kernels for RAW-layout factor pairs (row-major as a checkpoint has them; any size, any leading
+// dimension, element alignment), fp32, bf16 or fp16 storage with fp32 arithmetic:
 //   C[M x N] = A[M x K] . B[K x N]            (one stage of y = (x U) V, Sec. 4.1)
 // and, for the GLU sub-layer, C = silu(A1 . B1) * (A2 . B2) in one pass.
-// These kernels are the correctness baseline of the library (small fp32 case, odd
-// shapes); the packed MFMA kernels are the fast path.
 #pragma once
 #include "common.h"
 
 namespace deinfer {
 
-constexpr int GT = 64;   // output tile edge
-constexpr int GK = 16;   // k step
-constexpr int GTHREADS = 256;
-
-// Accumulate a 64x64 tile of A.B into acc (4x4 per thread).
-template <typename TA, typename TB>
-__device__ __forceinline__ void tile_gemm_rr(const TA *__restrict__ A, int64_t lda,
-                                             const TB *__restrict__ B, int64_t ldb,
-                                             int M, int N, int K, int m0, int n0,
-                                             float (&acc)[4][4], float (*sA)[GT + 1], float (*sB)[GT]) {
-  const int tid = threadIdx.x;
-  const int tx = tid & 15, ty = tid >> 4;
-  for (int k0 = 0; k0 < K; k0 += GK) {
-    // A tile: 64 rows x 16 k  -> sA[k][row]
-#pragma unroll
-    for (int i = 0; i < (GT * GK) / GTHREADS; ++i) {
-      int idx = tid + i * GTHREADS;
-      int r = idx / GK, c = idx % GK;
-      int gr = m0 + r, gc = k0 + c;
-      sA[c][r] = (gr < M && gc < K) ? Elem<TA>::load(A + (int64_t)gr * lda + gc) : 0.0f;
-    }
-    // B tile: 16 k x 64 cols -> sB[k][col]
-#pragma unroll
-    for (int i = 0; i < (GT * GK) / GTHREADS; ++i) {
-      int idx = tid + i * GTHREADS;
-      int r = idx / GT, c = idx % GT;
-      int gr = k0 + r, gc = n0 + c;
-      sB[r][c] = (gr < K && gc < N) ? Elem<TB>::load(B + (int64_t)gr * ldb + gc) : 0.0f;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < GK; ++kk) {
-      float a[4], b[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = sA[kk][ty * 4 + i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) b[j] = sB[kk][tx * 4 + j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-    }
-    __syncthreads();
-  }
+// How the product is laid on the matrix cores: 16x16x4 fp32 products (256 flops per clock and compute unit,
+// twice the vector rate; every operand is converted to fp32 exactly, so nothing is rounded before the sum).
+// A wavefront owns (16 MB) rows x (16 NV) columns and reads both operands from memory straight into the
+// registers the product wants, no LDS and no barrier in the loop:
+//   * a step is 16 k: lane l works for the k-group g = l / 16 on k = 4 g .. 4 g + 3, so the A operand of four
+//     products is one load of 4 consecutive elements of row l % 16;
+//   * B rows are read NV elements per lane: lane l holds columns NV (l % 16) .. + NV - 1 of row 4 g + e, and
+//     product j takes element j, i.e. column block j is the columns NV c + j.  A load instruction covers
+//     16 NV consecutive columns of four rows, and a lane ends up with NV consecutive output columns.
+// The wavefronts of a workgroup share one tile and split its k range; their sums meet in LDS, in wavefront
+// order (deterministic).  A 64 x 64 tile reads 16 bytes per clock and compute unit at the full matrix rate,
+// half of what a compute unit takes in from L2.  What bounds it: the fp32 matrix rate (157 TFLOP/s) for
+// many rows, the stream of B and the latency of the first loads for few.
+template <typename T> struct RawStore { typedef uint16_t type; };
+template <> struct RawStore<float> { typedef float type; };
+// (loads of several elements need no more than element alignment)
+template <typename T, int N> struct RawVec {
+  typedef typename RawStore<T>::type type __attribute__((ext_vector_type(N), aligned(sizeof(T))));
+};
+template <typename T> __device__ __forceinline__ float raw_cvt(typename RawStore<T>::type v) {
+  if constexpr (sizeof(T) == 4) return v;
+  else return cvt_in<DtOf<T>::value>(v);
 }
 
-// C = act(A.B + bias), or (DUAL) C = silu(A.B) * (A2.B2).  Grid: (ceil(N/64), ceil(M/64)).
+template <typename TA, typename TB> struct RawOperands {
+  const TA *A;
+  int64_t lda;
+  const TB *B;
+  int64_t ldb;
+  int K;
+};
+
+// register buffers of k-steps in flight: about 16 KiB per wavefront for the large tiles (the loads of a step
+// are requested 2 x 2000 matrix cycles ahead), more steps where a step is small
+constexpr int raw_depth(int mb, int nv) { return mb * nv >= 16 ? 3 : mb * nv >= 8 ? 4 : 6; }
+
+// acc[i][j] += A[m0 + 16 i .., :] . B[:, column block j of n0 ..], this wavefront's part of the k range.
+// EDGE: the tile reaches beyond column N - 1 (columns clamped; what they give is not stored).
+template <typename TA, typename TB, int MB, int NV, int NW, bool EDGE>
+__device__ __forceinline__ void raw_product(const RawOperands<TA, TB> &P, int M, int N, int64_t m0, int64_t n0, f32x4_t (&acc)[MB][NV]) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  typedef typename RawVec<TA, 4>::type AV;
+  typedef typename RawVec<TB, NV>::type BV;
+  typedef typename RawStore<TB>::type BS;
+  typedef typename RawStore<TA>::type AS;
+  constexpr int D = raw_depth(MB, NV);
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int c = lane & 15, g = lane >> 4;
+  const int steps = (P.K + 15) / 16, full = P.K / 16;
+  const int s_begin = (int)((int64_t)steps * wave / NW), s_end = (int)((int64_t)steps * (wave + 1) / NW);
+  const AS *a[MB];
+#pragma unroll
+  for (int i = 0; i < MB; ++i) {
+    int64_t row = m0 + 16 * i + c;
+    row = row < M ? row : M - 1;                       // (rows beyond M - 1 are not stored)
+    a[i] = reinterpret_cast<const AS *>(P.A) + row * P.lda + 4 * g;
+  }
+  int64_t col[EDGE ? NV : 1];
+#pragma unroll
+  for (int j = 0; j < (EDGE ? NV : 1); ++j) {
+    col[j] = n0 + NV * c + j;
+    if (EDGE && col[j] >= N) col[j] = N - 1;
+  }
+  const BS *b = reinterpret_cast<const BS *>(P.B) + (int64_t)(4 * g) * P.ldb;
+  struct Step { AV a[MB]; BV b[4]; } buf[D];
+  // part e of a step's loads: B rows 4 g + e and the A rows of every fourth row block
+  auto load = [&](Step &t, int s, int e) {
+    const BS *p = b + ((int64_t)16 * s + e) * P.ldb;
+    if constexpr (EDGE) {
+#pragma unroll
+      for (int j = 0; j < NV; ++j) t.b[e][j] = p[col[j]];
+    } else {
+      t.b[e] = *reinterpret_cast<const BV *>(p + col[0]);
+    }
+    if (e < MB) t.a[e] = *reinterpret_cast<const AV *>(a[e] + (int64_t)16 * s);
+  };
+  auto multiply = [&](const Step &t, int e) {
+#pragma unroll
+    for (int j = 0; j < NV; ++j)
+#pragma unroll
+      for (int i = 0; i < MB; ++i)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(raw_cvt<TA>(t.a[i][e]), raw_cvt<TB>(t.b[e][j]), acc[i][j], 0, 0, 0);
+  };
+  const bool tail = s_end == steps && full < steps;
+  const int s_stop = s_end < full ? s_end : full;
+  const int last = s_stop - 1;                         // (requests past the end repeat the last step)
+  // the last K % 16 of the k range: zeros beyond K - 1 (what is read there is row K - 1 and is replaced)
+  Step rest;
+  if (tail) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      int k = 16 * full + 4 * g + e;
+      k = k < P.K ? k : P.K - 1;
+#pragma unroll
+      for (int i = 0; i < MB; ++i) rest.a[i][e] = a[i][k - 4 * g];
+#pragma unroll
+      for (int j = 0; j < NV; ++j) rest.b[e][j] = b[(int64_t)(k - 4 * g) * P.ldb + (EDGE ? col[EDGE ? j : 0] : col[0] + j)];
+    }
+  }
+  if (s_begin < s_stop) {
+#pragma unroll
+    for (int d = 0; d < D - 1; ++d)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        load(buf[d], s_begin + d < last ? s_begin + d : last, e);
+        __builtin_amdgcn_sched_barrier(0);             // (in this order: the waits of the loop count on it)
+      }
+  }
+  if (tail) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const bool in = 16 * full + 4 * g + e < P.K;
+#pragma unroll
+      for (int i = 0; i < MB; ++i) rest.a[i][e] = in ? rest.a[i][e] : AS{};
+#pragma unroll
+      for (int j = 0; j < NV; ++j) rest.b[e][j] = in ? rest.b[e][j] : BS{};
+      multiply(rest, e);
+    }
+  }
+  if (s_begin < s_stop) {
+    int s = s_begin;
+    // Step s is multiplied while step s + D - 1 is requested, a quarter behind each quarter of the products.
+    // (No exit inside a round of D steps: with one, the compiler waits for every outstanding load at the top.)
+    for (; s + D <= s_stop; s += D) {
+#pragma unroll
+      for (int d = 0; d < D; ++d)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          multiply(buf[d], e);
+          __builtin_amdgcn_sched_barrier(0);
+          load(buf[(d + D - 1) % D], s + d + D - 1 < last ? s + d + D - 1 : last, e);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+#pragma unroll
+    for (int d = 0; d < D - 1; ++d)
+      if (s + d < s_stop) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) multiply(buf[d], e);
+      }
+  }
+#else
+  (void)P; (void)M; (void)N; (void)m0; (void)n0; (void)acc;
+#endif
+}
+
+// C = act(A.B + bias), or (DUAL) C = silu(A.B) * (A2.B2).  One workgroup of NW wavefronts = one tile of
+// 16 MB rows x 16 NV columns; the tiles of a column block are consecutive workgroups (they share B's columns).
 // bias: one value per column of C (may be null), act: see act_f32.
-template <typename TA, typename TB, typename TC, bool DUAL>
-__global__ __launch_bounds__(GTHREADS) void gemm_generic_kernel(
-    const TA *__restrict__ A, int64_t lda, const TB *__restrict__ B, int64_t ldb, int K,
-    const TA *__restrict__ A2, int64_t lda2, const TB *__restrict__ B2, int64_t ldb2, int K2,
-    TC *__restrict__ C, int64_t ldc, int M, int N, const TC *__restrict__ bias = nullptr, int act = ACT_NONE) {
-  __shared__ float sA[GK][GT + 1];
-  __shared__ float sB[GK][GT];
-  const int m0 = blockIdx.y * GT, n0 = blockIdx.x * GT;
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  float acc[4][4] = {};
-  tile_gemm_rr<TA, TB>(A, lda, B, ldb, M, N, K, m0, n0, acc, sA, sB);
-  float acc2[4][4] = {};
-  if (DUAL) tile_gemm_rr<TA, TB>(A2, lda2, B2, ldb2, M, N, K2, m0, n0, acc2, sA, sB);
+template <typename TA, typename TB, typename TC, bool DUAL, int MB, int NV, int NW>
+__global__ __launch_bounds__(64 * NW) void raw_gemm_kernel(
+    const RawOperands<TA, TB> P, const RawOperands<TA, TB> P2, TC *__restrict__ C, int64_t ldc, int M, int N,
+    const TC *__restrict__ bias, int act) {
+  constexpr int UNITS = 4 * MB;                        // accumulator element e of row block i: unit 4 i + e
+  constexpr int UPW = (UNITS + NW - 1) / NW;           // units that a wavefront sums and stores
+  typedef float sum_t __attribute__((ext_vector_type(NV)));
+  __shared__ sum_t part[NW][UNITS][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t m0 = (int64_t)blockIdx.x * (16 * MB), n0 = ((int64_t)blockIdx.z * gridDim.y + blockIdx.y) * (16 * NV);
+  if (n0 >= N) return;                                 // (the last slice of the column blocks)
+  const bool edge = n0 + 16 * NV > N;
+  float sum[DUAL ? 2 : 1][UPW][NV];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    int r = m0 + ty * 4 + i;
-    if (r >= M) continue;
+  for (int q = 0; q < (DUAL ? 2 : 1); ++q) {
+    f32x4_t acc[MB][NV];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      int c = n0 + tx * 4 + j;
-      if (c >= N) continue;
-      float v = acc[i][j];
-      if (DUAL) v = (v / (1.0f + expf(-v))) * acc2[i][j];
-      else v = act_f32(v + (bias ? Elem<TC>::load(bias + c) : 0.0f), act);
-      Elem<TC>::store(C + (int64_t)r * ldc + c, v);
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int j = 0; j < NV; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    if (edge) raw_product<TA, TB, MB, NV, NW, true>(q ? P2 : P, M, N, m0, n0, acc);
+    else raw_product<TA, TB, MB, NV, NW, false>(q ? P2 : P, M, N, m0, n0, acc);
+    if (q) __syncthreads();                            // the first product's sums have been read
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        sum_t v;
+#pragma unroll
+        for (int j = 0; j < NV; ++j) v[j] = acc[i][j][e];
+        part[wave][4 * i + e][lane] = v;
+      }
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < UPW; ++t) {
+      const int u = wave + t * NW;
+#pragma unroll
+      for (int j = 0; j < NV; ++j) sum[q][t][j] = 0.f;
+      if (u < UNITS) {
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+          const sum_t v = part[w][u][lane];
+#pragma unroll
+          for (int j = 0; j < NV; ++j) sum[q][t][j] += v[j];
+        }
+      }
+    }
+  }
+  const int64_t col0 = n0 + NV * (lane & 15);
+#pragma unroll
+  for (int t = 0; t < UPW; ++t) {
+    const int u = wave + t * NW;
+    const int64_t row = m0 + 16 * (u >> 2) + 4 * (lane >> 4) + (u & 3);
+    if (u >= UNITS || row >= M) continue;
+    float v[NV];
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+      const float z = sum[0][t][j];
+      if constexpr (DUAL) v[j] = (z / (1.0f + expf(-z))) * sum[DUAL ? 1 : 0][t][j];
+      else v[j] = act_f32(z + ((bias && col0 + j < N) ? Elem<TC>::load(bias + col0 + j) : 0.0f), act);
+    }
+    TC *dst = C + row * ldc + col0;
+    if (col0 + NV <= N) {
+      typedef typename RawVec<TC, NV>::type CV;
+      CV o;
+#pragma unroll
+      for (int j = 0; j < NV; ++j) {
+        if constexpr (sizeof(TC) == 4) o[j] = v[j];
+        else o[j] = cvt_out<DtOf<TC>::value>(v[j]);
+      }
+      *reinterpret_cast<CV *>(dst) = o;
+    } else {
+#pragma unroll
+      for (int j = 0; j < NV; ++j)
+        if (col0 + j < N) Elem<TC>::store(dst + j, v[j]);
     }
   }
 }

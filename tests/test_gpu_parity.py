@@ -94,6 +94,45 @@ def test_group_calls_raw(dn, dtype):
     assert max_err(to_host(h), rh) <= TOL[dtype]
 
 
+def in_nan(t, pad):
+    """The tensor inside a buffer of NaN: `pad` elements in front, rows `pad` elements longer (0: as it is)."""
+    import torch
+    d = to_dev(t)
+    if not pad:
+        return d
+    m, n = d.shape
+    buf = torch.full((pad + m * (n + pad),), float("nan"), dtype=d.dtype, device="cuda")
+    v = buf[pad:].view(m, n + pad)[:, :n]
+    v.copy_(d)
+    return v
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+@pytest.mark.parametrize("pad", [0, 3])
+@pytest.mark.parametrize("T,d_in,r,d_out", [
+    (5, 700, 21, 66),          # one 16 x 16 tile column at a time, k shared by 16 wavefronts; k = 21 in the second stage
+    (101, 301, 1001, 37),      # 16 x 32 tiles
+    (63, 131, 4090, 15),       # 32 x 32
+    (201, 47, 1638, 1643),     # 64 x 32
+    (205, 19, 4092, 4076),     # 64 x 64 where the rows are aligned to four elements
+    (1025, 17, 2044, 51),      # 32 x 64, likewise
+])
+def test_raw_tiles(dn, dtype, pad, T, d_in, r, d_out):
+    """Every tile of the RAW kernel at ragged edges; operands in the middle of NaN (nothing beyond a row's valid
+    columns enters a sum) at element alignment.  The bars are those of the other tests (fp32 sums; the
+    intermediate of this path is fp32 for every storage type)."""
+    x, U, V = gen(11, T, d_in, r, d_out, dtype)
+    p = dn.raw_pair(in_nan(U, pad), in_nan(V, pad))
+    xd = in_nan(x, pad)
+    y = dn.deinfer_lowrank_linear(xd, p, ws_for(dn, T, [p]))
+    ref = oracle.lowrank_linear(x.values, U.values, V.values)
+    assert max_err(to_host(y), ref) <= TOL[dtype]
+    g = dn.raw_pair(in_nan(si.make(12, 1, (d_in, r), 1.0 / np.sqrt(d_in), dtype), pad), in_nan(si.make(12, 2, (r, d_out), 1.0 / np.sqrt(r), dtype), pad))
+    h = dn.deinfer_lowrank_gateup_silu(xd, g, p, ws_for(dn, T, [g, p]))
+    gate = oracle.lowrank_linear(x.values, si.make(12, 1, (d_in, r), 1.0 / np.sqrt(d_in), dtype).values, si.make(12, 2, (r, d_out), 1.0 / np.sqrt(r), dtype).values)
+    assert max_err(to_host(h), gate / (1 + np.exp(-gate)) * ref) <= TOL[dtype]
+
+
 # ------------------------------------------------------------------ packed bf16, decode-sized
 DECODE_T = [1, 5, 16, 17, 33, 64, 100, 128]
 
