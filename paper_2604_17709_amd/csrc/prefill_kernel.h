@@ -65,6 +65,15 @@ template <int CMAX, int LPS, int EXTRA>
 struct PfVmWait<CMAX, CMAX, LPS, EXTRA> {
   static __device__ __forceinline__ void run(int) { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(CMAX * LPS + EXTRA) : "memory"); }
 };
+// Launches with at most this many token blocks give every XCD (workgroup index mod 8) a contiguous run of tiles:
+// the token blocks of a feature block then share one L2, which fetches the weights once; dealt out in turn,
+// every token block's XCD fetches them for itself (4 x the weights at 4 token blocks).  With 16 or more token
+// blocks a run would hold as many activation panels as the other order holds weight panels.
+constexpr int PF_RUN_TBLOCKS = 8;
+__device__ __forceinline__ int pf_tile_of(int bid, int n) {
+  const int xcd = bid & 7, q = n >> 3, rem = n & 7;
+  return xcd * q + (xcd < rem ? xcd : rem) + (bid >> 3);       // XCDs 0 .. rem - 1 have one tile more
+}
 constexpr int PF_XPITCH = PF_BK * 2;       // bytes per token row of the activation tile in LDS
 
 struct PfSeg {             // a run of 16-feature tiles that belongs to one factor
@@ -134,7 +143,7 @@ struct PfShared {
 constexpr int PF_POST_NONE = 0, PF_POST_BIAS_ACT = 1, PF_POST_TAIL = 2;
 
 template <int DT, int MF, bool GLU, int POSTK, bool SPLIT, bool ROPE, int TB>
-__device__ __forceinline__ void prefill_body(const PfParams &P, const int bid, const int n_tblocks, const int fb_shift) {
+__device__ __forceinline__ void prefill_body(const PfParams &P, const int bid, const int n_tiles, const int n_tblocks, const int fb_shift) {
   constexpr bool POST = POSTK == PF_POST_BIAS_ACT, TAIL = POSTK == PF_POST_TAIL;
   static_assert(!(ROPE && (GLU || POST || SPLIT)), "the rotary epilogue goes with a plain product");
   static_assert(!(TAIL && SPLIT), "only a second stage reads caller rows");
@@ -149,11 +158,12 @@ __device__ __forceinline__ void prefill_body(const PfParams &P, const int bid, c
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wf = wave & 1, wt = wave >> 1;         // wavefront position: features x tokens
 
-  // consecutive workgroups share a feature block and differ in the token block: the token
-  // blocks of one feature block run at the same time, spread over the XCDs, so each L2
-  // streams those weights once
-  const int tb = bid % n_tblocks;
-  const int fb_all = bid / n_tblocks + fb_shift;
+  // Tiles in order share a feature block and differ in the token block.  Workgroups go to the eight XCDs
+  // in turn, so with a multiple of 8 token blocks an XCD keeps a few token blocks and runs through the
+  // features.  With few token blocks (pf_tile_of) every XCD takes a contiguous run of tiles instead.
+  const int tile = n_tblocks <= PF_RUN_TBLOCKS ? pf_tile_of(bid, n_tiles) : bid;
+  const int tb = tile % n_tblocks;
+  const int fb_all = tile / n_tblocks + fb_shift;
   int fb = SPLIT ? fb_all % P.n_fblocks : fb_all;
   int pi = 0;                                                   // which product (uniform)
   if (!SPLIT && P.n_prob > 1 && fb >= P.fb0[1]) pi = 1;
@@ -568,13 +578,13 @@ __device__ __forceinline__ void prefill_body(const PfParams &P, const int bid, c
     }
   }
 #else
-  (void)P; (void)bid; (void)n_tblocks; (void)fb_shift;
+  (void)P; (void)bid; (void)n_tiles; (void)n_tblocks; (void)fb_shift;
 #endif
 }
 
 template <int DT, int MF, bool GLU, int POST = PF_POST_NONE, bool SPLIT = false, bool ROPE = false, int TB = 4>
 __global__ __launch_bounds__(PF_THREADS) void prefill_kernel(const PfParams P) {
-  prefill_body<DT, MF, GLU, POST, SPLIT, ROPE, TB>(P, (int)blockIdx.x, P.n_tblocks, 0);
+  prefill_body<DT, MF, GLU, POST, SPLIT, ROPE, TB>(P, (int)blockIdx.x, (int)gridDim.x, P.n_tblocks, 0);
 }
 
 // One launch with two tile shapes: the first P.n_big workgroups take 256 x 256 tiles of the feature
@@ -584,8 +594,8 @@ __global__ __launch_bounds__(PF_THREADS) void prefill_kernel(const PfParams P) {
 // large tile's time each.
 template <int DT, bool GLU, int POST, bool ROPE>
 __global__ __launch_bounds__(PF_THREADS) void prefill_mixed_kernel(const PfParams P) {
-  if ((int)blockIdx.x < P.n_big) prefill_body<DT, 8, GLU, POST, false, ROPE, 4>(P, (int)blockIdx.x, P.n_tblocks, 0);
-  else prefill_body<DT, 8, GLU, POST, false, ROPE, 2>(P, (int)blockIdx.x - P.n_big, P.n_tblocks2, P.fb_shift2);
+  if ((int)blockIdx.x < P.n_big) prefill_body<DT, 8, GLU, POST, false, ROPE, 4>(P, (int)blockIdx.x, P.n_big, P.n_tblocks, 0);
+  else prefill_body<DT, 8, GLU, POST, false, ROPE, 2>(P, (int)blockIdx.x - P.n_big, (int)gridDim.x - P.n_big, P.n_tblocks2, P.fb_shift2);
 }
 
 }  // namespace deinfer
