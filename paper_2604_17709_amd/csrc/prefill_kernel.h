@@ -79,6 +79,9 @@ constexpr int PF_XPITCH = PF_BK * 2;       // bytes per token row of the activat
 struct PfSeg {             // a run of 16-feature tiles that belongs to one factor
   const uint4 *frags;      // its packed fragments [tiles][KB][64]
   int tile0;               // first tile of the segment on the concatenated feature axis
+  int width2;              // optional second copy of the segment's first width2 columns (rank-space output) ...
+  uint16_t *out2;          // ... or null; 16-byte aligned rows (plain products only: no GLU, POST, ROPE, SPLIT)
+  long long ldo2;
 };
 
 struct PfProblem {         // one product  act[T x K] . W^T
@@ -562,6 +565,39 @@ __device__ __forceinline__ void prefill_body(const PfParams &P, const int bid, c
     if (ROPE && bt + 2 < NBATCH) load_tab(bt + 2);
     if (bt + 1 < NBATCH) read_batch(bt + 1, d[(bt + 1) & 1]);
     store_batch(bt, d[bt & 1]);
+  }
+  // Second copy of rank-space columns (t_k, t_v): this lane's chunk lies in one segment (whole 16-feature
+  // tiles).  As a copy launch of its own (one element per thread) each of them read t back and took 19 us for
+  // 8192 x 1228.  After the other stores, from the LDS tile once more: beside them it cost the plain kernels
+  // registers that they do not have.
+  if constexpr (!GLU && POSTK == PF_POST_NONE && !ROPE && !SPLIT) {
+    uint16_t *dst2 = nullptr;
+    long long ldo2 = 0;
+    int n2 = 0;                                    // valid columns of the chunk in the second copy
+#pragma unroll
+    for (int g = 0; g < 3; ++g)
+      if (g < Q.n_seg && lane_on && (col >> 4) >= Q.seg[g].tile0) {
+        const int col2 = col - Q.seg[g].tile0 * 16;
+        ldo2 = Q.seg[g].ldo2;
+        n2 = Q.seg[g].out2 != nullptr ? Q.seg[g].width2 - col2 : 0;
+        dst2 = Q.seg[g].out2 + (long long)tok_base * ldo2 + col2;
+      }
+    if (n2 > 0) {
+#pragma unroll 4
+      for (int q = 0; q < NQ; ++q) {
+        if (tok_base + q * RPI >= P.T) break;
+        const int row = q * RPI + rsub;
+        const u32x4_t d = *reinterpret_cast<const u32x4_t *>(E + row * PITCH + ((c ^ eswz(row)) * 16));
+        uint16_t *o = dst2 + (long long)(q * RPI) * ldo2;
+        if (n2 >= 8) {
+          *reinterpret_cast<u32x4_t *>(o) = d;
+        } else {
+#pragma unroll
+          for (int e = 0; e < 7; ++e)
+            if (e < n2) o[e] = (uint16_t)((d[e >> 1] >> ((e & 1) * 16)) & 0xffffu);
+        }
+      }
+    }
   }
   // rare: output rows that are not 16-byte aligned, or the valid columns end inside this chunk
   if (lane_on && !wide) {

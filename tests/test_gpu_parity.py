@@ -477,6 +477,36 @@ def test_keys_rebuilt_from_the_low_rank_cache(dn, T):
     assert max_err(to_host(k2), to_host(k).astype(np.float64)) <= 2.0 ** -7    # at most an output rounding apart
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("T,ranks", [(129, (24, 7, 96)), (256, (130, 37, 1)), (300, (264, 250, 270)), (1100, (40, 300, 513))])
+def test_rank_space_rows_stored_by_the_tile(dn, dtype, T, ranks):
+    """t_k, t_v of a first stage without a k-split: 16-byte aligned rows are stored with the tile, others copied
+    from t.  Both forms hold the same bits, the product's value, and write nothing beside the r columns."""
+    import torch
+    d_in = 264
+    F = [gen(60 + i, T, d_in, r, 72, dtype) for i, r in enumerate(ranks)]
+    x = F[0][0]
+    P = [pair(dn, U, V, packed=True) for _, U, V in F]
+    p = [q[0] for q in P]
+    ws = ws_for(dn, T, p)
+    xd = to_dev(x)
+    got = []
+    for shift, extra in ((0, 0), (3, 5)):                 # aligned rows; odd start and pitch
+        room, rows = [], []
+        for r in ranks[1:]:
+            pitch = (r + 7) // 8 * 8 + 8 + extra
+            buf = torch.full((shift + T * pitch,), 7.0, dtype=xd.dtype, device="cuda")
+            room.append(buf[shift:].view(T, pitch))
+            rows.append(room[-1][:, :r])
+        dn.deinfer_lowrank_qkv(xd, *p, ws, t_k=rows[0], t_v=rows[1])
+        for m, t, (_, U, _) in zip(room, rows, F[1:]):
+            assert bool((m[:, t.shape[1]:] == 7.0).all())
+            assert max_err(to_host(t.contiguous()), x.values.astype(np.float64) @ U.values.astype(np.float64)) <= TOL[dtype]
+        got.append([t.contiguous() for t in rows])
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
+
+
 # ------------------------------------------------------------------ non-GLU sub-layer: bias and activation
 @pytest.mark.parametrize("act", [0, 1, 2])
 @pytest.mark.parametrize("kind,T,d_in,r,d_out", [
