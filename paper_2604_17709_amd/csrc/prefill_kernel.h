@@ -14,22 +14,26 @@
 // time); a 256-row t tile does not fit the 160 KB LDS at these ranks.
 //
 // Tiling: 256 threads = 4 wavefronts (2 x 2), one per SIMD, workgroup tile 256 tokens x
-// (32 * MF) features; each wavefront owns 128 tokens x (16 * MF) features as (MF / 2) x 4
-// accumulator blocks of the 32x32x16 bf16 MFMA (features = MFMA rows, tokens = MFMA columns).
-// MF = 8 uses all 256 accumulator registers.  (The 16x16x32 form of the instruction issued at
-// only about 60 % of the rate of the 32x32x16 form in a bare issue-rate measurement on this
-// device, which is why the wider form is used although the packed fragments are 16 features
-// tall: a 32-feature operand is gathered from two neighbouring fragments by LDS addressing.)
+// (32 * MF) features; each wavefront owns 128 tokens x (16 * MF) features as MF x 8 accumulator
+// blocks of the 16x16x32 MFMA (features = MFMA rows, tokens = MFMA columns).  MF = 8 uses all 256
+// accumulation registers.
 // Both operands go from global memory straight into LDS (buffer loads with the LDS modifier,
 // 16 bytes per lane, 1 KiB contiguous in LDS per wavefront instruction, no staging registers):
-// weight fragments are already contiguous 1 KiB pieces; an activation tile is kept as 64-byte
-// token rows whose four 16-byte slots are XOR-swizzled with (row >> 2) & 3, applied on the
-// global side of the load (lane -> slot is fixed, lane -> k-chunk is permuted), which makes the
-// operand reads (16 rows x 16 bytes per quarter-wave) conflict free without padding.
-// Pipeline: one stage = one 32-wide k-block; four LDS stage buffers; the loads of stage s + 3
-// are requested while stage s is multiplied (about 2.5 stages = 2500 MFMA cycles of cover for
-// L2 misses); one barrier per stage, placed in the middle of the stage's products so that the
-// feature fragments of stage s + 1 can be read from LDS during the second half of stage s.
+// weight fragments are already contiguous 1 KiB pieces; activations come as 128-byte token rows,
+// the two k-blocks of a pair of stages at once, whose eight 16-byte slots are XOR-swizzled with
+// (row / 2) % 8, applied on the global side of the load (lane -> slot is fixed, lane -> k-chunk is
+// permuted), which keeps the operand reads free of bank conflicts without padding.
+// What bounds the loop beside the products is the number of requests to L2.  One k-block per row
+// and load (64 bytes, half a cache line) made every row two requests: 384 per 256 x 256 tile and
+// stage, by TCP_TCC_READ_REQ; whole lines make it 256.  7B block, 512 tokens 295 -> 271 us (its GLU
+// launch 70 -> 61 us), 8192 tokens 1749 -> 1627 us; 70B at 4096 tokens 2426 -> 2321 us; 13B at 8256
+// 2820 -> 2740 us; cached keys and values of 8192 tokens 243 -> 230 us.  (Rows whose pitch or first
+// column is no multiple of 128 bytes keep part of the second requests.)
+// Pipeline: one stage = one 32-wide k-block; the weights of stage s + 3 and half of the activations
+// of the pair that starts three or four stages later are requested while stage s is multiplied
+// (four weight buffers of 16 KiB, three activation buffers of 32 KiB: all 160 KiB of LDS); one
+// barrier per stage, placed in the middle of the stage's products so that the feature fragments of
+// stage s + 1 can be read from LDS during the second half of stage s.
 #pragma once
 #include <type_traits>
 #include "common.h"
@@ -53,18 +57,6 @@ constexpr int PF_STAGES_MF4 = 6;           // ... of the 128 x 128 tile (four st
                                            // compute unit, measured 3-7 % slower on launches of 32-128 tiles; eight the same as six)
 constexpr int pf_stages(int tb, int mf = 8) { return tb == 4 ? PF_STAGES : mf == 8 ? PF_STAGES_TB2 : PF_STAGES_MF4; }
 
-// s_waitcnt vmcnt(k * LPS + EXTRA) for a run-time k in [C, CMAX] (the instruction takes an immediate)
-template <int C, int CMAX, int LPS, int EXTRA>
-struct PfVmWait {
-  static __device__ __forceinline__ void run(int k) {
-    if (k == C) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(C * LPS + EXTRA) : "memory");
-    else PfVmWait<C + 1, CMAX, LPS, EXTRA>::run(k);
-  }
-};
-template <int CMAX, int LPS, int EXTRA>
-struct PfVmWait<CMAX, CMAX, LPS, EXTRA> {
-  static __device__ __forceinline__ void run(int) { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(CMAX * LPS + EXTRA) : "memory"); }
-};
 // Launches with at most this many token blocks give every XCD (workgroup index mod 8) a contiguous run of tiles:
 // the token blocks of a feature block then share one L2, which fetches the weights once; dealt out in turn,
 // every token block's XCD fetches them for itself (4 x the weights at 4 token blocks).  With 16 or more token
@@ -74,7 +66,8 @@ __device__ __forceinline__ int pf_tile_of(int bid, int n) {
   const int xcd = bid & 7, q = n >> 3, rem = n & 7;
   return xcd * q + (xcd < rem ? xcd : rem) + (bid >> 3);       // XCDs 0 .. rem - 1 have one tile more
 }
-constexpr int PF_XPITCH = PF_BK * 2;       // bytes per token row of the activation tile in LDS
+constexpr int PF_XPITCH = PF_BK * 4;       // bytes per token row of the activation tile in LDS: the k-blocks of two stages
+constexpr int pf_xpairs(int tb, int mf = 8) { return pf_stages(tb, mf) / 2 + 1; }     // activation buffers (two stages each)
 
 struct PfSeg {             // a run of 16-feature tiles that belongs to one factor
   const uint4 *frags;      // its packed fragments [tiles][KB][64]
@@ -123,7 +116,7 @@ struct PfParams {
 template <int MF, int TB = 4>
 struct PfShared {
   uint4 w[pf_stages(TB, MF)][2 * MF][64];                   // [stage][feature tile][lane]
-  unsigned char x[pf_stages(TB, MF)][64 * TB * PF_XPITCH];  // [stage][token row * 64 bytes], slots swizzled
+  unsigned char x[pf_xpairs(TB, MF)][64 * TB * PF_XPITCH];  // [pair of stages][token row * 128 bytes], slots swizzled
 };
 
 // GLU = true: two products per tile, P.prob[0] (gate) and P.prob[1] (up, same feature tiles and output):
@@ -216,17 +209,25 @@ __device__ __forceinline__ void prefill_body(const PfParams &P, const int bid, c
       wtile_off[i] = live ? (unsigned)(gt - Q.seg[sgi].tile0) * (unsigned)Q.KB * 1024u : 0u;
     }
     const unsigned wlane = lane * 16;
-    // activations: instruction i of wavefront w covers tile rows 16 (4 i + w) .. + 15; lane l holds
-    // slot l % 4 of row l / 4 and fetches k-chunk slot ^ ((row >> 2) & 3) = (l & 3) ^ ((l >> 4) & 3)
+    // activations: both k-blocks of a pair of stages at once, whole 128-byte lines.  Instruction i (0 .. 2 TB - 1)
+    // of wavefront w covers tile rows 8 (4 i + w) .. + 7; lane l holds slot l % 8 of row l / 8 and fetches k-chunk
+    // slot ^ (row / 2) % 8 = (l & 7) ^ (4 (w & 1) + l / 16)
     const __amdgpu_buffer_rsrc_t xres =
         __builtin_amdgcn_make_buffer_rsrc((void *)Q.act, 0, (int)((unsigned)P.T * (unsigned)(Q.lda * 2)), 0x00020000);
-    const int chunk = (lane & 3) ^ ((lane >> 4) & 3);
-    unsigned xrow[TB];
-#pragma unroll
-    for (int i = 0; i < TB; ++i) xrow[i] = (unsigned)(tok0 + 16 * (4 * i + wave) + (lane >> 2)) * (unsigned)(Q.lda * 2);
+    const int chunk = (lane & 7) ^ (((wave & 1) << 2) | (lane >> 4));
+    const unsigned xrow = (unsigned)(tok0 + 8 * wave + (lane >> 3)) * (unsigned)(Q.lda * 2);
+    const unsigned xstep = 32u * (unsigned)(Q.lda * 2);
     const int n_stages = SPLIT ? (Q.KB - kb0 < P.kb_per_part ? Q.KB - kb0 : P.kb_per_part) : Q.KB;
 
-    // one load instruction (index 0 .. LPS - 1) of stage st: weight tiles first, then activation rows.
+    constexpr int D = NST - 1;             // weight loads run D stages ahead of the products
+    constexpr int XM = (D + 1) / 2;        // activation loads run XM pairs of stages ahead
+    constexpr int NXP = pf_xpairs(TB, MF);
+    static_assert(NXP == XM + 1, "the buffer of the pair before is free");
+    constexpr unsigned DEAD = 0x80000000u; // lane offset of a load that is not needed: beyond every descriptor, reads zeros
+    // One load instruction (index 0 .. LPS - 1) of slot sl, the loads that go out beside the products of stage sl:
+    // the weight tiles of stage sl + D, then the first (sl even) or second half of the activation rows of pair
+    // sl / 2 + XM.  Every slot issues all of its loads, those past the last stage as DEAD ones: the load counter is
+    // the same in every stage.
     // Activation chunks beyond K re-read a chunk of valid columns (the last one; PF_POST_TAIL: the first one),
     // which meets zero weights.
     const unsigned xchunk = (unsigned)(chunk * 16);
@@ -237,58 +238,63 @@ __device__ __forceinline__ void prefill_body(const PfParams &P, const int bid, c
     // beyond K - 1 are set to zero (lds_zero_chunk_tail in common.h).  -1: nothing to do (every other call).
     const int krem = Q.K & 7;
     const int st_fix = (TAIL && krem != 0) ? (Q.K >> 5) - kb0 : -1;
-    auto fix_tail = [&](int buf) {
+    auto fix_tail = [&] {
       int row = threadIdx.x;
       asm volatile("" : "+v"(row));
-      if (row < 64 * TB) lds_zero_chunk_tail(&S.x[buf][row * PF_XPITCH + ((((Q.K >> 3) & 3) ^ ((row >> 2) & 3)) * 16)], krem);
+      if (row < 64 * TB)
+        lds_zero_chunk_tail(&S.x[(st_fix >> 1) % NXP][row * PF_XPITCH + (((4 * (st_fix & 1) + ((Q.K >> 3) & 3)) ^ ((row >> 1) & 7)) * 16)], krem);
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
       __builtin_amdgcn_s_barrier();
       asm volatile("" ::: "memory");
     };
-    auto fetch_part = [&](int st, int idx) {
-      const int buf = st % NST;
+    auto fetch_part = [&](int sl, int idx, auto sure) {          // sure: the stages it belongs to exist
+      constexpr bool SURE = decltype(sure)::value;
       if (idx < WT) {
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(wres[idx], (DEINFER_LOCAL void *)&S.w[buf][uwave * WT + idx][0], 16,
-                                                 wlane, wtile_off[idx] + (unsigned)(st + kb0) * 1024u, 0, 0);
+        const int st = sl + D;
+        const unsigned dead = SURE || st < n_stages ? 0u : DEAD;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(wres[idx], (DEINFER_LOCAL void *)&S.w[st % NST][uwave * WT + idx][0], 16,
+                                                 wlane | dead, wtile_off[idx] + (unsigned)(st + kb0) * 1024u, 0, 0);
       } else {
-        const int i = idx - WT;
-        unsigned kb = (unsigned)(st + kb0) * (PF_BK * 2) + xchunk;
+        const int pair = (sl >> 1) + XM, i = (sl & 1) * TB + idx - WT;
+        const unsigned dead = SURE || 2 * pair < n_stages ? 0u : DEAD;
+        unsigned kb = (unsigned)(2 * pair + kb0) * (PF_BK * 2) + xchunk;
         kb = TAIL ? (kb < xkend ? kb : 0u) : (kb < xklim ? kb : xklim);
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(xres, (DEINFER_LOCAL void *)&S.x[buf][16 * (4 * i + uwave) * PF_XPITCH], 16,
-                                                 xrow[i] + kb, 0, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(xres, (DEINFER_LOCAL void *)&S.x[pair % NXP][8 * (4 * i + uwave) * PF_XPITCH], 16,
+                                                 (xrow + (unsigned)i * xstep + kb) | dead, 0, 0, 0);
       }
     };
     // Operand reads for the 16x16x32 product: lane l works on row (feature or token) l % 16 and on the 8
     // consecutive k of group l / 16.  A packed 16-feature fragment is in that order already.
-    const int b_off = (wt * WTOK + (lane & 15)) * PF_XPITCH + (((lane >> 4) ^ ((lane >> 2) & 3)) * 16);
+    // A row's two k-blocks: slots 0 .. 3 and 4 .. 7 before the swizzle, i.e. 64 bytes apart by exclusive or.  The
+    // swizzle keeps the 16 lanes that the LDS serves at once (0-3, 12-15, 20-27 and so on: two k-groups) on 16
+    // different groups of four banks.
+    const int b_off = (wt * WTOK + (lane & 15)) * PF_XPITCH + (((lane >> 4) ^ ((lane >> 1) & 7)) * 16);
     auto read_a = [&](int buf, int i) -> u32x4_t { return *reinterpret_cast<const u32x4_t *>(&S.w[buf][wf * MF + i][lane]); };
-    auto read_b = [&](int buf, int j) -> u32x4_t {
-      return *reinterpret_cast<const u32x4_t *>(&S.x[buf][b_off + 16 * j * PF_XPITCH]);
+    auto read_b = [&](int xbuf, int odd, int j) -> u32x4_t {
+      return *reinterpret_cast<const u32x4_t *>(&S.x[xbuf][(b_off ^ (64 * odd)) + 16 * j * PF_XPITCH]);
     };
-    constexpr int D = NST - 1;             // loads run D stages ahead of the products
-    constexpr int H1 = LPS / 2;            // loads 0 .. H1 - 1 of stage s + D go out in the second half of stage s,
+    constexpr int H1 = LPS / 2;            // loads 0 .. H1 - 1 of slot s go out in the second half of stage s,
                                            // loads H1 .. LPS - 1 in the first half of stage s + 1
+    const std::true_type yes;
+    const std::false_type no;
     static_assert((D - 2) * LPS + H1 < 64, "the load counter has 6 bits");
-    // stages 0 .. D - 2 whole and the first half of stage D - 1, then wait for stage 0
+    // the first half of pair 0, slots -D .. -2 whole and the first half of slot -1, then wait for stage 0
 #pragma unroll
-    for (int sg = 0; sg < D - 1; ++sg)
-      if (sg < n_stages) {
+    for (int i = WT; i < LPS; ++i) fetch_part(-D - 1, i, yes);
 #pragma unroll
-        for (int i = 0; i < LPS; ++i) fetch_part(sg, i);
-      }
-    if (D - 1 < n_stages) {
+    for (int sl = -D; sl < -1; ++sl) {
 #pragma unroll
-      for (int i = 0; i < H1; ++i) fetch_part(D - 1, i);
+      for (int i = 0; i < LPS; ++i) fetch_part(sl, i, no);
     }
+#pragma unroll
+    for (int i = 0; i < H1; ++i) fetch_part(-1, i, no);
     between();
-    // outstanding at most: the stages after stage 0 (and the half stage D - 1)
-    if (D - 1 < n_stages) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((D - 2) * LPS + H1) : "memory");
-    else PfVmWait<0, D - 2, LPS, 0>::run(n_stages - 1);
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((D - 2) * LPS + H1) : "memory");    // slot -D has arrived
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();          // stage 0 has landed everywhere
     asm volatile("" ::: "memory");
     if constexpr (TAIL) {
-      if (st_fix == 0) fix_tail(0);
+      if (st_fix == 0) fix_tail();
     }
     // A stage is TJ groups of MF products that share one token operand (a group: 16 cycles per product).
     // Token operands are read two groups ahead of their use into a ring of four, the feature operands of
@@ -296,17 +302,16 @@ __device__ __forceinline__ void prefill_body(const PfParams &P, const int bid, c
     u32x4_t a0[MF], a1[MF], b[4];
 #pragma unroll
     for (int i = 0; i < MF; ++i) a0[i] = read_a(0, i);
-    b[0] = read_b(0, 0);
-    b[1] = read_b(0, 1);
-    // One stage: feature operands in `a`, those of the next stage into `an`.  STEADY: stage st + D exists
-    // (no conditions in the loop body).  At most two memory instructions follow a product: their issue
+    b[0] = read_b(0, 0, 0);
+    b[1] = read_b(0, 0, 1);
+    // One stage: feature operands in `a`, those of the next stage into `an`; odd = st % 2.  STEADY: every stage
+    // that the slot's loads belong to exists.  At most two memory instructions follow a product: their issue
     // hides behind the products' cycles in the matrix pipeline.
-    auto stage = [&](int st, u32x4_t (&a)[MF], u32x4_t (&an)[MF], auto steady) {
+    auto stage = [&](int st, u32x4_t (&a)[MF], u32x4_t (&an)[MF], auto odd_t, auto steady) {
       constexpr bool STEADY = decltype(steady)::value;
-      const int buf = st % NST;
+      constexpr int ODD = decltype(odd_t)::value;
       const int nbuf = (st + 1) % NST;
-      const bool i2 = STEADY || st + D - 1 < n_stages;     // second part of stage st + D - 1 still to request
-      const bool i3 = STEADY || st + D < n_stages;         // stage st + D exists
+      const int xbuf = (st >> 1) % NXP, nxbuf = ((st + 1) >> 1) % NXP;
       constexpr int HG = TJ / 2, HN = HG * MF;             // groups / products of half a stage
       constexpr int AN = MF / HG;                          // next-stage feature operands read per group of the second half
       auto half = [&](auto second) {
@@ -322,10 +327,10 @@ __device__ __forceinline__ void prefill_body(const PfParams &P, const int bid, c
 #pragma unroll
             for (int l = 0; l < NL; ++l)
               if (l * HN / NL == n) {
-                if (SECOND) { if (i3) fetch_part(st + D, l); }
-                else if (i2) fetch_part(st + D - 1, H1 + l);
+                if (SECOND) fetch_part(st, l, steady);
+                else fetch_part(st - 1, H1 + l, steady);
               }
-            if (i == 1) b[(g + 2) & 3] = g + 2 < TJ ? read_b(buf, g + 2) : read_b(nbuf, g + 2 - TJ);
+            if (i == 1) b[(g + 2) & 3] = g + 2 < TJ ? read_b(xbuf, ODD, g + 2) : read_b(nxbuf, 1 - ODD, g + 2 - TJ);
             if (SECOND) {
 #pragma unroll
               for (int t = 0; t < AN; ++t)
@@ -336,43 +341,41 @@ __device__ __forceinline__ void prefill_body(const PfParams &P, const int bid, c
         }
       };
       half(std::false_type{});
-      // stage st + 1 has landed (this wavefront's part) once at most the loads of the stages st + 2 .. st + D - 1
-      // are outstanding; after the barrier it has landed everywhere and nobody reads the buffer of stage st - 1
-      // any more, which is where stage st + D goes.  A bare barrier: the wait is the only ordering needed
-      // (loads into LDS are complete when the counter says so); the fence of __syncthreads() would drain
+      // stage st + 1 has landed (this wavefront's part) once at most the loads of the slots st - D + 2 .. st - 1 are
+      // outstanding (its weights are in slot st + 1 - D, its activations in slots up to that one); after the
+      // barrier it has landed everywhere and nobody reads the weights of stage st - 1 or the activations of the
+      // pair before this one any more, whose buffers slot st fills.  A bare barrier: the wait is the only ordering
+      // needed (loads into LDS are complete when the counter says so); the fence of __syncthreads() would drain
       // every outstanding load instead.
-      if (STEADY) {
-        asm volatile("s_waitcnt vmcnt(%0)" ::"n"((D - 2) * LPS) : "memory");
-      } else {
-        int rem = n_stages - (st + 2);
-        rem = rem < 0 ? 0 : rem > D - 2 ? D - 2 : rem;
-        PfVmWait<0, D - 2, LPS, 0>::run(rem);
-      }
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"((D - 2) * LPS) : "memory");
       asm volatile("" ::: "memory");
       __builtin_amdgcn_s_barrier();
       asm volatile("" ::: "memory");
       // (the chunk that holds column K - 1 is in the last stage: only stages without a whole pipeline behind
       // them can precede it, so the steady-state loop carries no branch for this)
       if constexpr (TAIL && !STEADY) {
-        if (st + 1 == st_fix) fix_tail(nbuf);              // (uniform)
+        if (st + 1 == st_fix) fix_tail();                  // (uniform)
       }
       // (after the last stage the reads ahead hit a stage buffer nobody writes any more; the values are unused)
       half(std::true_type{});
     };
     {
-      const std::true_type yes;
-      const std::false_type no;
+      const std::integral_constant<int, 0> even;
+      const std::integral_constant<int, 1> odd;
       int st = 0;
+      // (the loads of slot st + 1: weights of stage st + 1 + D, activations of stages up to st + 2 XM + 1 = st + D + 2;
+      // the last of these may not exist: its columns are clamped to the row's valid ones and are not multiplied)
       for (; st + 1 + D < n_stages; st += 2) {
-        stage(st, a0, a1, yes);
-        stage(st + 1, a1, a0, yes);
+        stage(st, a0, a1, even, yes);
+        stage(st + 1, a1, a0, odd, yes);
       }
       for (; st < n_stages; st += 2) {
-        stage(st, a0, a1, no);
+        stage(st, a0, a1, even, no);
         if (st + 1 >= n_stages) break;
-        stage(st + 1, a1, a0, no);
+        stage(st + 1, a1, a0, odd, no);
       }
     }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // the DEAD loads write zeros: before anything else uses the buffers
     mfma_settle(acc);
   };
   if constexpr (GLU) {

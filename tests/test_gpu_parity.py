@@ -477,6 +477,25 @@ def test_keys_rebuilt_from_the_low_rank_cache(dn, T):
     assert max_err(to_host(k2), to_host(k).astype(np.float64)) <= 2.0 ** -7    # at most an output rounding apart
 
 
+@pytest.mark.parametrize("pad", [0, 24])
+@pytest.mark.parametrize("kb", [1, 2, 3, 4, 5, 6, 7, 8, 9, 15])
+def test_compute_bound_pipeline_depths(dn, kb, pad):
+    """k ranges from a single k-block (shorter than the pipeline) over odd and even counts, in both stages; activation
+    rows on whole cache lines and (pad: 48 bytes longer) not.  What lies behind the rows is NaN."""
+    import torch
+    T, d_in, r, d_out = 259, 32 * kb - 8, 32 * kb - 3, 136
+    x, U, V = gen(70 + kb, T, d_in, r, d_out, "bf16")
+    p, keep = pair(dn, U, V, packed=True)
+    buf = torch.full((T, (d_in + 63) // 64 * 64 + 64 + pad), float("nan"), dtype=torch.bfloat16, device="cuda")
+    xd = buf[:, :d_in]
+    xd.copy_(to_dev(x))
+    y = dn.deinfer_lowrank_linear(xd, p, ws_for(dn, T, [p]))
+    ref = oracle.lowrank_linear(x.values, U.values, V.values)
+    assert max_err(to_host(y), ref) <= TOL["bf16"]
+    h = dn.deinfer_lowrank_gateup_silu(xd, p, p, ws_for(dn, T, [p, p]))
+    assert max_err(to_host(h), ref / (1 + np.exp(-ref)) * ref) <= 2 * TOL["bf16"]    # two factors, each within the bar
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("T,ranks", [(129, (24, 7, 96)), (256, (130, 37, 1)), (300, (264, 250, 270)), (1100, (40, 300, 513))])
 def test_rank_space_rows_stored_by_the_tile(dn, dtype, T, ranks):
