@@ -78,6 +78,13 @@ __device__ __forceinline__ float act_f32(float z, int act) {
   return z;
 }
 
+// Workgroups go to the eight XCDs (each with its own L2) in turn.  The tile of workgroup bid of n where every
+// XCD takes a contiguous run of tiles.
+__device__ __forceinline__ int run_tile_of(int bid, int n) {
+  const int xcd = bid & 7, q = n >> 3, rem = n & 7;
+  return xcd * q + (xcd < rem ? xcd : rem) + (bid >> 3);       // XCDs 0 .. rem - 1 have one tile more
+}
+
 // value of the lane 8 further round the same row of 16 lanes (lane ^ 8); every lane of the row must be active
 __device__ __forceinline__ uint32_t across8(uint32_t v) {
 #if defined(__HIP_DEVICE_COMPILE__)

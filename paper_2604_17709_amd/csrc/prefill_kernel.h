@@ -62,10 +62,6 @@ constexpr int pf_stages(int tb, int mf = 8) { return tb == 4 ? PF_STAGES : mf ==
 // every token block's XCD fetches them for itself (4 x the weights at 4 token blocks).  With 16 or more token
 // blocks a run would hold as many activation panels as the other order holds weight panels.
 constexpr int PF_RUN_TBLOCKS = 8;
-__device__ __forceinline__ int pf_tile_of(int bid, int n) {
-  const int xcd = bid & 7, q = n >> 3, rem = n & 7;
-  return xcd * q + (xcd < rem ? xcd : rem) + (bid >> 3);       // XCDs 0 .. rem - 1 have one tile more
-}
 constexpr int PF_XPITCH = PF_BK * 4;       // bytes per token row of the activation tile in LDS: the k-blocks of two stages
 constexpr int pf_xpairs(int tb, int mf = 8) { return pf_stages(tb, mf) / 2 + 1; }     // activation buffers (two stages each)
 
@@ -156,8 +152,8 @@ __device__ __forceinline__ void prefill_body(const PfParams &P, const int bid, c
 
   // Tiles in order share a feature block and differ in the token block.  Workgroups go to the eight XCDs
   // in turn, so with a multiple of 8 token blocks an XCD keeps a few token blocks and runs through the
-  // features.  With few token blocks (pf_tile_of) every XCD takes a contiguous run of tiles instead.
-  const int tile = n_tblocks <= PF_RUN_TBLOCKS ? pf_tile_of(bid, n_tiles) : bid;
+  // features.  With few token blocks (run_tile_of) every XCD takes a contiguous run of tiles instead.
+  const int tile = n_tblocks <= PF_RUN_TBLOCKS ? run_tile_of(bid, n_tiles) : bid;
   const int tb = tile % n_tblocks;
   const int fb_all = tile / n_tblocks + fb_shift;
   int fb = SPLIT ? fb_all % P.n_fblocks : fb_all;

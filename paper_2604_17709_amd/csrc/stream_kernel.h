@@ -1,9 +1,9 @@
-// Memory-bound kernel for a stage with many output features (T <= 64 tokens, PACKED bf16 pairs):
+// Memory-bound kernel for a stage of a call of T <= 128 tokens (PACKED 16-bit pairs):
 // no partial sums leave the workgroup, so the stage is ONE launch with its epilogue inside.
 //
 //   out[T x F] = act[T x K] . W^T,  W packed as [tiles][KB][64] fragments (Sec. 4.1, either stage)
 //
-// One workgroup = one block of 32 features; its four wavefronts split the k range of that block
+// One workgroup = one block of 32 features (and of 32 NB tokens); its four wavefronts split the k range of that block
 // ("split-r reduction through LDS"): each streams its quarter of the block's weights straight into
 // registers (non-temporal, every byte is used once) and keeps its own [T x 64 k] activation slabs
 // in its own LDS region (global -> LDS loads, 64-byte rows with XOR-swizzled 16-byte slots).
@@ -13,7 +13,12 @@
 // The four accumulator sets are added through LDS and the epilogue (bf16 rounding, optional second
 // copy of t, SiLU-GLU) writes the final output.  For the GLU call the workgroup owns 32 output
 // columns: wavefronts 0, 1 take the two k halves of the gate block, 2, 3 those of the up block.
-// Activation traffic is T / 32 times the weight traffic (2 x at T = 64) and comes from L2.
+// Activation traffic is as much as the weight traffic per 32 tokens and comes from L2.
+// More tokens than a workgroup holds are further workgroups (StParams::n_tblocks): short stages, where the
+// loads of a whole wavefront's k range are a few round trips, gain more from one launch without partial
+// sums than the weights' second and fourth reading (from the XCD's L2) costs.  One upward projection at
+// 128 tokens against split + reduce: 1024 features, k = 512: 9.7 -> 5.3 us, k = 1640: 11.7 -> 9.1 us; 8192
+// features, k = 1024: 18.5 -> 15.4 us (k = 1640: 21.2 -> 26.8 us, left to the split).
 #pragma once
 #include "common.h"
 #include "skinny_kernel.h"
@@ -48,6 +53,7 @@ struct StProblem {           // one product
 
 struct StParams {
   int T;
+  int n_tblocks;             // blocks of 32 NB tokens
   int n_prob;
   int glu;                   // 1: prob[0] = gate, prob[1] = up (same shapes); output silu(gate) * up through prob[0]
   StProblem prob[3];
@@ -66,7 +72,11 @@ __global__ __launch_bounds__(ST_THREADS, 2) void stream_kernel(const StParams P)
   static_assert(4 * ST_SLOTS * SLAB >= 4 * NB * 4 * 64 * 16, "the reduction buffer fits the slab space");
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int blk = blockIdx.x;
+  // token blocks of a feature block next to each other on one XCD: its L2 fetches their weights once
+  const int tile = P.n_tblocks > 1 ? run_tile_of((int)blockIdx.x, (int)gridDim.x) : (int)blockIdx.x;
+  const int blk = tile / P.n_tblocks;
+  const int tok0 = (tile - blk * P.n_tblocks) * (32 * NB);
+  const int n_tok = P.T - tok0 < 32 * NB ? P.T - tok0 : 32 * NB;
   int pi = 0;
   if (!P.glu) {
     if (P.n_prob > 1 && blk >= P.prob[1].block0) pi = 1;
@@ -96,14 +106,14 @@ __global__ __launch_bounds__(ST_THREADS, 2) void stream_kernel(const StParams P)
                              ? wtile * (unsigned)Q.KB * 1024u + (unsigned)(((lane & 15) + 16 * (lane >> 5)) * 16) : OOB;
   // ---- activations: 16 rows x 64 bytes per load instruction; lane l holds slot l % 4 of row l / 4
   // and fetches k-chunk slot ^ ((row >> 2) & 3)
-  const unsigned xbytes = (unsigned)(((long long)(P.T - 1) * Q.lda + ((Q.K + 7) & ~7)) * 2);
-  const __amdgpu_buffer_rsrc_t xres = __builtin_amdgcn_make_buffer_rsrc((void *)Q.act, 0, (int)xbytes, 0x00020000);
+  const unsigned xbytes = (unsigned)(((long long)(n_tok - 1) * Q.lda + ((Q.K + 7) & ~7)) * 2);
+  const __amdgpu_buffer_rsrc_t xres = __builtin_amdgcn_make_buffer_rsrc((void *)(Q.act + (long long)tok0 * Q.lda), 0, (int)xbytes, 0x00020000);
   constexpr int NXI = NB * 2;                          // load instructions per k-block
   unsigned xrow[NXI];
 #pragma unroll
   for (int i = 0; i < NXI; ++i) {
     const int row = 16 * i + (lane >> 2);
-    xrow[i] = row < P.T ? (unsigned)row * (unsigned)(Q.lda * 2) : OOB;
+    xrow[i] = row < n_tok ? (unsigned)row * (unsigned)(Q.lda * 2) : OOB;
   }
   const unsigned xchunk = (unsigned)((((lane & 3) ^ ((lane >> 4) & 3))) * 16);
   const unsigned xkend = (unsigned)(((Q.K + 7) >> 3) * 16);      // bytes of a row up to the end of the chunk that holds column K - 1
@@ -213,7 +223,7 @@ __global__ __launch_bounds__(ST_THREADS, 2) void stream_kernel(const StParams P)
       v[0] = (s0.x + s1.x) + (s2.x + s3.x); v[1] = (s0.y + s1.y) + (s2.y + s3.y);
       v[2] = (s0.z + s1.z) + (s2.z + s3.z); v[3] = (s0.w + s1.w) + (s2.w + s3.w);
     }
-    const int tok = 32 * j + (lane & 31);
+    const int tok = tok0 + 32 * j + (lane & 31);
     const int col = fblk * 32 + 8 * q + 4 * (lane >> 5);
     if (!P.glu && (P.bias != nullptr || P.act != ACT_NONE)) {
 #pragma unroll

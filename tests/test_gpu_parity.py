@@ -477,6 +477,33 @@ def test_keys_rebuilt_from_the_low_rank_cache(dn, T):
     assert max_err(to_host(k2), to_host(k).astype(np.float64)) <= 2.0 ** -7    # at most an output rounding apart
 
 
+@pytest.mark.parametrize("T", [9, 17, 33, 64, 65, 97, 128])
+@pytest.mark.parametrize("d_in,r,d_out", [
+    (264, 37, 40),          # one launch per stage, a few workgroups
+    (1000, 1021, 200),      # ... k ends inside the last short k-block range
+    (1032, 500, 4100),      # first stage: by the number of workgroups; second: 129 blocks
+    (72, 250, 8200),        # 257 blocks: more than the compute units, left to the split
+    (4200, 1037, 136),      # both stages split over k, with the reduce launch
+])
+def test_decode_stages_by_token_blocks(dn, T, d_in, r, d_out):
+    """Both sides of the choice between one launch of token blocks and the k-split, in both stages, with the
+    rank-space output, the GLU form and the upward projection alone on rows that end in NaN."""
+    import torch
+    x, U, V = gen(80, T, d_in, r, d_out, "bf16")
+    p, keep = pair(dn, U, V, packed=True)
+    ws = ws_for(dn, T, [p, p, p])
+    xd = to_dev(x)
+    buf = torch.full((T, (r + 7) // 8 * 8 + 8), float("nan"), dtype=torch.bfloat16, device="cuda")
+    tk = buf[:, :r]
+    q, k, v = dn.deinfer_lowrank_qkv(xd, p, p, p, ws, t_k=tk)
+    ref = oracle.lowrank_linear(x.values, U.values, V.values)
+    for y in (q, k, v, dn.deinfer_lowrank_linear(xd, p, ws), dn.deinfer_lowrank_up(tk, p, ws)):
+        assert max_err(to_host(y), ref) <= TOL["bf16"]
+    assert bool(torch.isnan(buf[:, r:]).all())
+    h = dn.deinfer_lowrank_gateup_silu(xd, p, p, ws_for(dn, T, [p, p]))
+    assert max_err(to_host(h), ref / (1 + np.exp(-ref)) * ref) <= 2 * TOL["bf16"]    # two factors, each within the bar
+
+
 @pytest.mark.parametrize("pad", [0, 24])
 @pytest.mark.parametrize("kb", [1, 2, 3, 4, 5, 6, 7, 8, 9, 15])
 def test_compute_bound_pipeline_depths(dn, kb, pad):
