@@ -219,11 +219,11 @@ __device__ __forceinline__ void prefill_body(const PfParams &P, const int bid, c
     constexpr int XM = (D + 1) / 2;        // activation loads run XM pairs of stages ahead
     constexpr int NXP = pf_xpairs(TB, MF);
     static_assert(NXP == XM + 1, "the buffer of the pair before is free");
-    constexpr unsigned DEAD = 0x80000000u; // lane offset of a load that is not needed: beyond every descriptor, reads zeros
+    constexpr unsigned DEAD = 0x80000000u; // lane offset of an activation load that is not needed: beyond every descriptor, reads zeros
     // One load instruction (index 0 .. LPS - 1) of slot sl, the loads that go out beside the products of stage sl:
     // the weight tiles of stage sl + D, then the first (sl even) or second half of the activation rows of pair
-    // sl / 2 + XM.  Every slot issues all of its loads, those past the last stage as DEAD ones: the load counter is
-    // the same in every stage.
+    // sl / 2 + XM.  Every slot issues all of its loads, those past the last stage as dead ones that read zeros: the
+    // load counter is the same in every stage.
     // Activation chunks beyond K re-read a chunk of valid columns (the last one; PF_POST_TAIL: the first one),
     // which meets zero weights.
     const unsigned xchunk = (unsigned)(chunk * 16);
@@ -247,9 +247,8 @@ __device__ __forceinline__ void prefill_body(const PfParams &P, const int bid, c
       constexpr bool SURE = decltype(sure)::value;
       if (idx < WT) {
         const int st = sl + D;
-        const unsigned dead = SURE || st < n_stages ? 0u : DEAD;
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(wres[idx], (DEINFER_LOCAL void *)&S.w[st % NST][uwave * WT + idx][0], 16,
-                                                 wlane | dead, wtile_off[idx] + (unsigned)(st + kb0) * 1024u, 0, 0);
+        const BufOffsets off = weight_load(SURE || st < n_stages, wlane, wtile_off[idx] + (unsigned)(st + kb0) * 1024u);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(wres[idx], (DEINFER_LOCAL void *)&S.w[st % NST][uwave * WT + idx][0], 16, off.lane, off.scalar, 0, 0);
       } else {
         const int pair = (sl >> 1) + XM, i = (sl & 1) * TB + idx - WT;
         const unsigned dead = SURE || 2 * pair < n_stages ? 0u : DEAD;
@@ -371,7 +370,7 @@ __device__ __forceinline__ void prefill_body(const PfParams &P, const int bid, c
         stage(st + 1, a1, a0, odd, no);
       }
     }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // the DEAD loads write zeros: before anything else uses the buffers
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // the dead loads write zeros: before anything else uses the buffers
     mfma_settle(acc);
   };
   if constexpr (GLU) {

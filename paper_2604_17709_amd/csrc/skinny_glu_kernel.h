@@ -54,7 +54,7 @@ __global__ __launch_bounds__(128 * NW, 1) void skinny_glu_kernel(const SkGluPara
   // a 128-byte row spans half of the banks: the slot is XORed with (row / 2) % 8 (see skinny_kernel.h)
   auto swz = [](int row) { return (row >> 1) & (SPR - 1); };
 
-  constexpr unsigned OOB = 0x7ffffff0u;
+  constexpr unsigned OOB = BUF_DEAD;
   const SkProblem &Q = prod == 0 ? P.gate : P.up;
   const int KBq = Q.KB;
   const unsigned wbytes = (unsigned)Q.n_ftiles * (unsigned)Q.KB * 1024u;
@@ -96,8 +96,8 @@ __global__ __launch_bounds__(128 * NW, 1) void skinny_glu_kernel(const SkGluPara
   auto fetch_one = [&](u32x4_t (&wn)[NWL], int fst, int fbuf, int idx) {
     if (idx < NWL) {
       const int kb = fst * KBS + (idx >> 1);
-      const unsigned off = kb < KBq ? wlane : OOB;                // k-blocks past the product's range read zeros
-      wn[idx] = __builtin_amdgcn_raw_buffer_load_b128(wres, off, kb * 1024 + (idx & 1) * 512, 2);
+      const BufOffsets off = weight_load(kb < KBq, wlane, (unsigned)kb * 1024u);   // (k-blocks past the product's range read zeros)
+      wn[idx] = __builtin_amdgcn_raw_buffer_load_b128(wres, off.lane + (idx & 1) * 512, off.scalar, 2);
     } else {
       const int i = idx - NWL;
       const unsigned dead = fst * KBS < KBq ? 0u : OOB;

@@ -120,9 +120,8 @@ __global__ __launch_bounds__(64 * NW, NW >= 3 ? 2 : 1) void skinny_kernel(const 
   const __amdgpu_buffer_rsrc_t wres = __builtin_amdgcn_make_buffer_rsrc((void *)Q.frags, 0, (int)wbytes, 0x00020000);
   // lane l holds feature l % 32 (tile 2 fblk + (l / 16) % 2, row l % 16) and k-group 2 s + l / 32
   const unsigned wtile = (unsigned)(2 * fblk + ((lane >> 4) & 1));
-  const unsigned wlane = wtile * (unsigned)Q.KB * 1024u + (unsigned)(((lane & 15) + 16 * (lane >> 5)) * 16);
-  const bool wtile_ok = (int)wtile < Q.n_ftiles;
-  constexpr unsigned OOB = 0x7ffffff0u;
+  constexpr unsigned OOB = BUF_DEAD;
+  const unsigned wlane = (int)wtile < Q.n_ftiles ? wtile * (unsigned)Q.KB * 1024u + (unsigned)(((lane & 15) + 16 * (lane >> 5)) * 16) : OOB;
   // ---- activations
   const unsigned xbytes = (unsigned)(((long long)(P.T - 1) * Q.lda + ((Q.K + 7) & ~7)) * 2);
   const __amdgpu_buffer_rsrc_t xres = __builtin_amdgcn_make_buffer_rsrc((void *)Q.act, 0, (int)xbytes, 0x00020000);
@@ -164,10 +163,10 @@ __global__ __launch_bounds__(64 * NW, NW >= 3 ? 2 : 1) void skinny_kernel(const 
 #pragma unroll
     for (int kbi = 0; kbi < KBS; ++kbi) {
       const int kb = kb_begin + st * KBS + kbi;
-      const unsigned off = (wtile_ok && kb < kb_end) ? wlane : OOB;
+      const BufOffsets off = weight_load(kb < kb_end, wlane, (unsigned)kb * 1024u);
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks)
-        w[kbi * 2 + ks] = __builtin_amdgcn_raw_buffer_load_b128(wres, off, kb * 1024 + ks * 512, 2);
+        w[kbi * 2 + ks] = __builtin_amdgcn_raw_buffer_load_b128(wres, off.lane + ks * 512, off.scalar, 2);
     }
   };
 
@@ -192,8 +191,8 @@ __global__ __launch_bounds__(64 * NW, NW >= 3 ? 2 : 1) void skinny_kernel(const 
   auto fetch_one = [&](u32x4_t (&wn)[KBS * 2], int fst, int fbuf, int idx) {
     if (idx < KBS * 2) {
       const int kb = kb_begin + fst * KBS + (idx >> 1);
-      const unsigned off = (wtile_ok && kb < kb_end) ? wlane : OOB;
-      wn[idx] = __builtin_amdgcn_raw_buffer_load_b128(wres, off, kb * 1024 + (idx & 1) * 512, 2);
+      const BufOffsets off = weight_load(kb < kb_end, wlane, (unsigned)kb * 1024u);
+      wn[idx] = __builtin_amdgcn_raw_buffer_load_b128(wres, off.lane + (idx & 1) * 512, off.scalar, 2);
     } else {
       const int i = idx - KBS * 2;
       const unsigned dead = fst < n_stages ? 0u : OOB;

@@ -97,7 +97,7 @@ __global__ __launch_bounds__(ST_THREADS, 2) void stream_kernel(const StParams P)
 
   // ---- weights: a lane offset beyond the descriptor's size reads zeros (tiles past the last one,
   // k-blocks past the range, slots past the last one) and costs no traffic
-  constexpr unsigned OOB = 0x7ffffff0u;
+  constexpr unsigned OOB = BUF_DEAD;
   const unsigned wbytes = (unsigned)Q.n_ftiles * (unsigned)Q.KB * 1024u;
   const __amdgpu_buffer_rsrc_t wres = __builtin_amdgcn_make_buffer_rsrc((void *)Q.frags, 0, (int)wbytes, 0x00020000);
   // lane l holds feature l % 32 (tile 2 fblk + (l / 16) % 2, row l % 16) and k-group 2 s + l / 32
@@ -130,9 +130,10 @@ __global__ __launch_bounds__(ST_THREADS, 2) void stream_kernel(const StParams P)
     for (int kbi = 0; kbi < ST_SKB; ++kbi) {
       const int kb = kb_begin + slot * ST_SKB + kbi;
       const bool live = kb < kb_end;                                 // uniform
+      const BufOffsets off = weight_load(live, wlane, (unsigned)kb * 1024u);
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks)
-        w[kbi * 2 + ks] = __builtin_amdgcn_raw_buffer_load_b128(wres, live ? wlane : OOB, kb * 1024 + ks * 512, 2);
+        w[kbi * 2 + ks] = __builtin_amdgcn_raw_buffer_load_b128(wres, off.lane + ks * 512, off.scalar, 2);
       // chunks beyond K re-read a chunk of valid columns (the last one; TAIL: the first one), which meets zero weights
       unsigned kbyte = (unsigned)kb * 64u + xchunk;
       kbyte = TAIL ? (kbyte < xkend ? kbyte : 0u) : (kbyte < xklim ? kbyte : xklim);
