@@ -491,13 +491,13 @@ def test_decode_stages_by_token_blocks(dn, T, d_in, r, d_out):
     import torch
     x, U, V = gen(80, T, d_in, r, d_out, "bf16")
     p, keep = pair(dn, U, V, packed=True)
-    ws = ws_for(dn, T, [p, p, p])
+    ws, ws1 = ws_for(dn, T, [p, p, p]), ws_for(dn, T, [p])    # (one pair alone may be cut into more k-ranges than three)
     xd = to_dev(x)
     buf = torch.full((T, (r + 7) // 8 * 8 + 8), float("nan"), dtype=torch.bfloat16, device="cuda")
     tk = buf[:, :r]
     q, k, v = dn.deinfer_lowrank_qkv(xd, p, p, p, ws, t_k=tk)
     ref = oracle.lowrank_linear(x.values, U.values, V.values)
-    for y in (q, k, v, dn.deinfer_lowrank_linear(xd, p, ws), dn.deinfer_lowrank_up(tk, p, ws)):
+    for y in (q, k, v, dn.deinfer_lowrank_linear(xd, p, ws1), dn.deinfer_lowrank_up(tk, p, ws1)):
         assert max_err(to_host(y), ref) <= TOL["bf16"]
     assert bool(torch.isnan(buf[:, r:]).all())
     h = dn.deinfer_lowrank_gateup_silu(xd, p, p, ws_for(dn, T, [p, p]))
