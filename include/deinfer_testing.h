@@ -61,6 +61,13 @@ int deinfer_set_prefill_feature_tile(int features);
 int deinfer_set_decode_glu_one_launch(int mode);
 
 /*
+ * The choice that a call on RAW pairs makes for one product [M x K] . [K x N] on a device of `compute_units` units
+ * (host only): tile[0] x tile[1] = rows x columns of a workgroup's tile, tile[2] = its wavefronts.  rows4: the rows of
+ * the second operand are aligned to four elements; dual: the product pair of a GLU call (K: the mean of the two).
+ */
+int deinfer_plan_raw_tile(int64_t M, int64_t N, int64_t K, int dtype, int rows4, int dual, int compute_units, int *tile);
+
+/*
  * What this device delivers on the two rooflines of the path (Sec. 5.2 "Throughput Analysis"
  * reports throughput only; the denominators are this build's), for a benchmark that prints a
  * measured ceiling beside the published one.  Both enqueue one kernel on `stream`, allocate

@@ -451,38 +451,50 @@ void launch_raw(const RawCall<TA, TB, TC, DUAL> &c, hipStream_t s) {
   hipLaunchKernelGGL((raw_gemm_kernel<TA, TB, TC, DUAL, MB, NV, NW>), dim3((unsigned)mt, (unsigned)(nt < SLICE ? nt : SLICE), (unsigned)ceil_div(nt, SLICE)),
                      dim3(64 * NW), 0, s, c.p, c.p2, c.C, c.ldc, (int)c.M, (int)c.N, c.bias, c.act);
 }
-// Tile of a product: the one with the smallest estimate  rounds of workgroups x time of one workgroup.  The
-// times (per k, relative) are those of the tiles in a launch that fills the device, 2048 x 1024 x 1024 in fp32:
-// 64 x 64 45.9 us, 32 x 64 45.4, 64 x 32 51.7, 32 x 32 65.6, 16 x 32 68, 16 x 16 88 us.  They predicted the fastest
-// or a tile within 10 % of it for 201 x 1638 x 4096 (64 x 32: 48 us, 64 x 64: 71), 201 x 4096 x 1638 (64 x 64: 32 us,
-// 16 x 16: 65), 64 x 4096 x 1638, 100 x 1000 x 300, 512 x 819 x 4096, 2048 x 300 x 700 and 1000 x 64 x 64.
+// Tile of a product: the one with the smallest estimate  rounds of workgroups x (k x time per k + epilogue), over
+// the compute units.  Times in units of one k of the 16 x 16 tile, for fp32 and for 16-bit B rows (which a 64 x 32
+// tile reads in 4-byte pieces), fitted to all six tiles timed on 1107 products (M = 1 .. 2048, N = 63 .. 4096,
+// k = 64 .. 4096, B rotated over more than 256 MB).  The choice is on average 0.8 % behind the best of the six and at
+// most 23 % (fp32 512 x 1024 x 4096: 64 x 32 53.6 us, 32 x 64 43.4).  201 x 1638 x 4096 in fp32: 64 x 32 49.2 us,
+// 64 x 64 64.6, 16 x 32 64.5; 201 x 4096 x 1638: 64 x 64 33.9 us, 32 x 64 39.5; in bf16 201 x 1638 x 1638: 16 x 32 22.5,
+// 64 x 32 38.0.
 // Tiles of 64 columns read four elements of a B row at once and need those rows aligned to the four (a row
-// pitch of 819 fp32 elements: 77 us for 512 x 819 x 4096 as 32 x 64 tiles against 49 as 64 x 32).
+// pitch of 819 fp32 elements: 77 us for 512 x 819 x 4096 as 32 x 64 tiles against 49 as 64 x 32); with two products
+// (dual) their sums would not leave room for them.
+struct RawTile { int mb, nv; double per_k, fixed; };
+constexpr RawTile RAW_TILES[2][6] = {
+    {{4, 4, 7.76, 182}, {2, 4, 4.36, 67}, {4, 2, 4.06, 131}, {2, 2, 2.55, 190}, {1, 2, 1.78, 142}, {1, 1, 1.0, 36}},       // fp32
+    {{4, 4, 11.28, 121}, {2, 4, 5.27, 148}, {4, 2, 6.74, 112}, {2, 2, 2.78, 199}, {1, 2, 1.62, 74}, {1, 1, 1.0, 36}}};     // 16 bits
+struct RawChoice { int mb, nv, nw; };
+RawChoice raw_choice(int64_t M, int64_t N, double k, bool fp32, bool rows4, bool dual, int cus) {
+  RawChoice best = {0, 0, 4};
+  double best_cost = 0;
+  for (const RawTile &t : RAW_TILES[fp32 ? 0 : 1]) {
+    if (t.nv == 4 && (!rows4 || dual)) continue;
+    const double cost = (double)ceil_div(ceil_div(M, 16 * t.mb) * ceil_div(N, 16 * t.nv), (int64_t)cus) * (t.per_k * k + t.fixed);
+    if (best.mb == 0 || cost < best_cost) { best.mb = t.mb; best.nv = t.nv; best_cost = cost; }
+  }
+  // few tiles and a long k: 16 wavefronts share the k range of a tile instead of four (k = 4096, one row, up to 64
+  // tiles: fp32 5 to 10 % faster, bf16 20 to 30; 16 rows: fp32 within 4 %, bf16 6 to 15 % faster; k = 1638, 16 rows:
+  // fp32 26 to 34 % slower)
+  if (best.mb == 1 && best.nv == 1 && 4 * ceil_div(M, 16) * ceil_div(N, 16) <= cus && k >= 4096) best.nw = 16;
+  return best;
+}
 template <typename TA, typename TB, typename TC, bool DUAL>
 int run_raw(const RawCall<TA, TB, TC, DUAL> &c, hipStream_t s, const char *what) {
   const int cus = device_cus();
   if (cus <= 0) return fail(DEINFER_ERR_DEVICE, "no usable HIP device");
   auto rows4 = [](const RawOperands<TA, TB> &p) { return aligned(p.B, 4 * sizeof(TB)) && p.ldb % 4 == 0; };
-  const bool wide = rows4(c.p) && (!DUAL || rows4(c.p2));
-  struct Tile { int mb, nv; double cost; };
-  static constexpr Tile tiles[] = {{4, 4, 0.172}, {2, 4, 0.085}, {4, 2, 0.097}, {2, 2, 0.0615}, {1, 2, 0.032}, {1, 1, 0.0205}};
-  int best = -1;
-  double best_cost = 0;
-  for (int i = 0; i < 6; ++i) {
-    if (tiles[i].nv == 4 && (!wide || DUAL)) continue;      // (two products: their sums would not leave room for those)
-    const double cost = (double)ceil_div(ceil_div(c.M, 16 * tiles[i].mb) * ceil_div(c.N, 16 * tiles[i].nv), (int64_t)cus) * tiles[i].cost;
-    if (best < 0 || cost < best_cost) { best = i; best_cost = cost; }
-  }
-  // few tiles and a long k: 16 wavefronts share the k range of a tile instead of four
-  const int64_t wgs = ceil_div(c.M, 16) * ceil_div(c.N, 16);
-  if (best == 5 && 4 * wgs <= cus && c.p.K >= 512) launch_raw<1, 1, 16>(c, s);
-  else if (best == 5) launch_raw<1, 1, 4>(c, s);
-  else if (best == 4) launch_raw<1, 2, 4>(c, s);
-  else if (best == 3) launch_raw<2, 2, 4>(c, s);
-  else if (best == 2) launch_raw<4, 2, 4>(c, s);
+  const double k = DUAL ? 0.5 * ((double)c.p.K + (double)c.p2.K) : (double)c.p.K;
+  const RawChoice t = raw_choice(c.M, c.N, k, sizeof(TB) == 4, rows4(c.p) && (!DUAL || rows4(c.p2)), DUAL, cus);
+  if (t.mb == 1 && t.nv == 1 && t.nw == 16) launch_raw<1, 1, 16>(c, s);
+  else if (t.mb == 1 && t.nv == 1) launch_raw<1, 1, 4>(c, s);
+  else if (t.mb == 1 && t.nv == 2) launch_raw<1, 2, 4>(c, s);
+  else if (t.mb == 2 && t.nv == 2) launch_raw<2, 2, 4>(c, s);
+  else if (t.mb == 4 && t.nv == 2) launch_raw<4, 2, 4>(c, s);
   if constexpr (!DUAL) {
-    if (best == 1) launch_raw<2, 4, 4>(c, s);
-    else if (best == 0) launch_raw<4, 4, 4>(c, s);
+    if (t.mb == 2 && t.nv == 4) launch_raw<2, 4, 4>(c, s);
+    else if (t.mb == 4 && t.nv == 4) launch_raw<4, 4, 4>(c, s);
   }
   return check_launch(what);
 }
@@ -748,6 +760,14 @@ int deinfer_set_prefill_token_tile(int tokens) {
 int deinfer_set_decode_glu_one_launch(int mode) {
   if (mode != 0 && mode != 1 && mode != -1) return fail(DEINFER_ERR_INVALID_ARG, "GLU second stage: 0, 1 or -1, got %d", mode);
   g_glu_width = mode;
+  return DEINFER_OK;
+}
+
+int deinfer_plan_raw_tile(int64_t M, int64_t N, int64_t K, int dtype, int rows4, int dual, int compute_units, int *tile) {
+  if (M < 1 || N < 1 || K < 1 || compute_units < 1 || !tile) return fail(DEINFER_ERR_INVALID_ARG, "raw tile: bad argument");
+  if (dtype != DEINFER_F32 && dtype != DEINFER_BF16 && dtype != DEINFER_F16) return fail(DEINFER_ERR_UNSUPPORTED, "raw tile: unknown dtype %d", dtype);
+  const RawChoice c = raw_choice(M, N, (double)K, dtype == DEINFER_F32, rows4 != 0, dual != 0, compute_units);
+  tile[0] = 16 * c.mb; tile[1] = 16 * c.nv; tile[2] = c.nw;
   return DEINFER_OK;
 }
 

@@ -9,6 +9,21 @@ from paper_2604_17709_amd import TOKEN_TILE_BOTH  # noqa: F401  (importing the b
 # bf16 and fp32: the stated bars; fp16: the bf16 bar scaled by the ratio of the unit roundoffs (2^-11 / 2^-8), rounded up
 TOL = {"bf16": 1e-2, "f16": 2e-3, "f32": 1e-5}
 
+# (T, d_in, r, d_out) of the test of the RAW kernel's tiles; tests/test_plans.py checks that on 256 compute units they
+# take every tile that the choice has, in both stages, for 32- and 16-bit pairs
+RAW_ROWS = [
+    (5, 700, 21, 66),          # 16 x 16; k = 21 in the second stage
+    (5, 4200, 21, 66),         # 16 x 16, k shared by 16 wavefronts
+    (4, 30, 4200, 66),         # ... in the second stage
+    (101, 301, 1001, 37),      # 16 x 16, in 16 bits 16 x 32
+    (63, 131, 4090, 15),       # 32 x 32
+    (201, 47, 1638, 1643),     # 64 x 32; second stage in 16 bits 16 x 32
+    (205, 19, 4092, 4076),     # rows aligned to four elements: 32 x 64 and 64 x 64 (in 16 bits the other way round)
+    (1025, 17, 2044, 51),      # 32 x 64 (64 x 64) likewise, then 16 x 32
+    (169, 33, 41, 1115),       # two products: 32 x 32
+    (325, 33, 17, 773),        # two products in 16 bits: 64 x 32
+]
+
 
 def to_dev(t: si.Tensor):
     import torch

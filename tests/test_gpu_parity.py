@@ -7,7 +7,7 @@ import pytest
 import oracle
 import synth_inputs as si
 from oracle import paged_cache as pc
-from gpu_util import TOKEN_TILE_BOTH, TOL, max_err, pair, to_dev, to_host
+from gpu_util import RAW_ROWS, TOKEN_TILE_BOTH, TOL, max_err, pair, to_dev, to_host
 
 pytestmark = pytest.mark.gpu
 
@@ -109,14 +109,7 @@ def in_nan(t, pad):
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
 @pytest.mark.parametrize("pad", [0, 3])
-@pytest.mark.parametrize("T,d_in,r,d_out", [
-    (5, 700, 21, 66),          # one 16 x 16 tile column at a time, k shared by 16 wavefronts; k = 21 in the second stage
-    (101, 301, 1001, 37),      # 16 x 32 tiles
-    (63, 131, 4090, 15),       # 32 x 32
-    (201, 47, 1638, 1643),     # 64 x 32
-    (205, 19, 4092, 4076),     # 64 x 64 where the rows are aligned to four elements
-    (1025, 17, 2044, 51),      # 32 x 64, likewise
-])
+@pytest.mark.parametrize("T,d_in,r,d_out", RAW_ROWS)
 def test_raw_tiles(dn, dtype, pad, T, d_in, r, d_out):
     """Every tile of the RAW kernel at ragged edges; operands in the middle of NaN (nothing beyond a row's valid
     columns enters a sum) at element alignment.  The bars are those of the other tests (fp32 sums; the
