@@ -235,13 +235,15 @@ __device__ __forceinline__ void prefill_body(const PfParams &P, const int bid, c
     const int krem = Q.K & 7;
     const int st_fix = (TAIL && krem != 0) ? (Q.K >> 5) - kb0 : -1;
     auto fix_tail = [&] {
-      int row = threadIdx.x;
-      asm volatile("" : "+v"(row));
-      if (row < 64 * TB)
-        lds_zero_chunk_tail(&S.x[(st_fix >> 1) % NXP][row * PF_XPITCH + (((4 * (st_fix & 1) + ((Q.K >> 3) & 3)) ^ ((row >> 1) & 7)) * 16)], krem);
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-      __builtin_amdgcn_s_barrier();
-      asm volatile("" ::: "memory");
+      if constexpr (TAIL) {
+        int row = threadIdx.x;
+        asm volatile("" : "+v"(row));
+        if (row < 64 * TB)
+          lds_zero_chunk_tail(&S.x[(st_fix >> 1) % NXP][row * PF_XPITCH + (((4 * (st_fix & 1) + ((Q.K >> 3) & 3)) ^ ((row >> 1) & 7)) * 16)], krem);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+      }
     };
     auto fetch_part = [&](int sl, int idx, auto sure) {          // sure: the stages it belongs to exist
       constexpr bool SURE = decltype(sure)::value;
@@ -422,30 +424,31 @@ __device__ __forceinline__ void prefill_body(const PfParams &P, const int bid, c
     return;
   }
   // accumulators -> bf16 pairs first (registers only): it overlaps the wait for the slowest wavefront.
-  // (GLU: not ahead of the barrier: 128 registers of pairs beside the 128 of the gate values would not
-  // fit; every pair is formed right before it is written to LDS instead)
-  uint2 pk[GLU ? 1 : MF][GLU ? 1 : TJ];
-  if constexpr (!GLU) {
+  // (GLU and POST: not ahead of the barrier.  128 registers of pairs do not fit beside the 128 of the gate values,
+  // nor, without a spill, beside the activation's temporaries: every pair is formed right before it is written to
+  // LDS instead)
+  constexpr bool LATE = GLU || POST;
+  uint2 pk[LATE ? 1 : MF][LATE ? 1 : TJ];
+  if constexpr (!LATE) {
 #pragma unroll
-    for (int i = 0; i < MF; ++i) {
-      float b[4] = {0.f, 0.f, 0.f, 0.f};
-      if (POST && Q.bias != nullptr) {
-        // element e of block (i, j) is feature 16 i + 4 (lane / 16) + e of this wavefront's 16 MF features
-        const int f0 = (fb * BF_TILES + wf_e * MF) * 16 + 16 * i + 4 * (lane_e >> 4);
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (f0 + e < Q.width) b[e] = cvt_in<DT>(Q.bias[f0 + e]);
-      }
+    for (int i = 0; i < MF; ++i)
 #pragma unroll
       for (int j = 0; j < TJ; ++j) {
-        float v[4] = {acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]};
-        if (POST) {
-#pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] = act_f32(v[e] + b[e], Q.post_act);
-        }
-        pk[GLU ? 0 : i][GLU ? 0 : j].x = pack2<DT>(v[0], v[1]);
-        pk[GLU ? 0 : i][GLU ? 0 : j].y = pack2<DT>(v[2], v[3]);
+        pk[LATE ? 0 : i][LATE ? 0 : j].x = pack2<DT>(acc[i][j][0], acc[i][j][1]);
+        pk[LATE ? 0 : i][LATE ? 0 : j].y = pack2<DT>(acc[i][j][2], acc[i][j][3]);
       }
+  }
+  // POST: the bias of this lane's features, four per feature block, on the way while the barrier is waited for:
+  // element e of block (i, j) is feature 16 i + 4 (lane / 16) + e of this wavefront's 16 MF features
+  uint2 bias[POST ? MF : 1];
+  if constexpr (POST) {
+#pragma unroll
+    for (int i = 0; i < MF; ++i) {
+      const int f0 = (fb * BF_TILES + wf_e * MF) * 16 + 16 * i + 4 * (lane_e >> 4);
+      uint16_t b[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) b[e] = Q.bias != nullptr && f0 + e < Q.width ? Q.bias[f0 + e] : (uint16_t)0;
+      bias[POST ? i : 0] = make_uint2((unsigned)b[0] | ((unsigned)b[1] << 16), (unsigned)b[2] | ((unsigned)b[3] << 16));
     }
   }
 
@@ -509,14 +512,21 @@ __device__ __forceinline__ void prefill_body(const PfParams &P, const int bid, c
           for (int e = 0; e < 4; ++e) asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(u[e]) : "a"(acc[i][j][e]));
           w.x = pack2<DT>(u[0] * lo_f32<DT>(sg.x), u[1] * hi_f32<DT>(sg.x));
           w.y = pack2<DT>(u[2] * lo_f32<DT>(sg.y), u[3] * hi_f32<DT>(sg.y));
+        } else if constexpr (POST) {
+          const uint2 b = bias[POST ? i : 0];
+          float v[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(v[e]) : "a"(acc[i][j][e]));
+          w.x = pack2<DT>(act_f32(v[0] + lo_f32<DT>(b.x), Q.post_act), act_f32(v[1] + hi_f32<DT>(b.x), Q.post_act));
+          w.y = pack2<DT>(act_f32(v[2] + lo_f32<DT>(b.y), Q.post_act), act_f32(v[3] + hi_f32<DT>(b.y), Q.post_act));
         } else {
-          w = pk[GLU ? 0 : i][GLU ? 0 : j];
+          w = pk[LATE ? 0 : i][LATE ? 0 : j];
         }
         // (the swizzle of row 16 j + wrow is that of wrow)
         *reinterpret_cast<uint2 *>(E + (16 * j + wrow) * PITCH + (((2 * i + wchunk) ^ eswz(wrow)) * 16) + whalf) = w;
         // (one pair at a time, in source order: scheduled freely, all 256 sums are read out of the
         // accumulator registers first, which does not fit beside the gate values)
-        if constexpr (GLU) __builtin_amdgcn_sched_barrier(0);
+        if constexpr (LATE) __builtin_amdgcn_sched_barrier(0);
       }
   }
   if (ROPE && NBATCH > 1) load_tab(1);
