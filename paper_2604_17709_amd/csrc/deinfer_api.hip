@@ -192,7 +192,7 @@ SkPlan skinny_plan(int64_t T, const deinfer_factors_t *const *f, int n, bool glu
 // range is then cut into parts (fp32 partial products, summed by the reduce kernel of the T <= 128
 // path).  Stage 2 (short k, many features) is left whole: its partial products would cost more than
 // they save.  The number of parts minimises an estimate of the launch time in units of one pipeline
-// stage of one tile (about 0.7 us): rounds of workgroups x (stages + epilogue) + the reduce launch.
+// stage of one tile: rounds of workgroups x (stages + epilogue) + the reduce launch.
 struct PfSplitPlan {
   int n_parts, kb_per_part, n_fblocks, n_tblocks;
   size_t part_bytes;          // 0: no split
@@ -210,22 +210,28 @@ PfSplitPlan prefill_split_plan(int64_t T, const deinfer_factors_t *const *f, int
   if (wgs <= 0 || KB < 16) return pl;
   const int cus_now = device_cus();
   const int64_t cus = cus_now > 0 ? cus_now : 256;
-  // measured on the device: epilogue of a tile that rounds and stores t (about 8 stages) or stores
-  // its fp32 partial products (about 20: 256 KiB per workgroup, all units at once); a 128 x 256 tile
-  // takes 0.64 of a 256 x 256 tile in the last round of a large launch and 0.78 in a launch of its own
-  // (70B shapes, o-projection at 4096 tokens: 138 us unsplit against 106 + 18 us as two parts); the reduce launch reads its partial products at about 0.3 us per
-  // MB (0.43 stages) after about 4 us (6 stages) of fixed cost
-  constexpr double E_PLAIN = 8.0, E_PART = 20.0, SMALL_TILE = 0.64, SMALL_TILES_ONLY = 0.78, REDUCE_PER_MB = 0.43, REDUCE_FIXED = 6.0;
+  // In pipeline stages of a 256 x 256 tile, which take 0.70 us in a launch that fills the device (256 tiles, k = 1024 /
+  // 4096 / 11008: 61 / 129 / 284 us).  The other figures were fitted to the times of 565 first stages (k = 1024 .. 28672,
+  // 256 .. 5096 columns, 129 .. 8192 tokens, the weights rotated over more than 256 MB) with every number of parts up
+  // to 16: epilogue of a tile that rounds and stores t (8) or stores its fp32 partial products (20: 256 KiB per
+  // workgroup, all units at once); a 128 x 256 tile takes 0.55 of a 256 x 256 tile in the last round of a large launch and
+  // 0.75 in a launch of its own, a 128 x 128 tile 0.5; the reduce launch 0.5 per MB of partial products after 6.5.  The
+  // number of parts chosen is on average 0.5 % behind the best and at most 14 % (11008 x 256 at 8192 tokens, 8 parts
+  // 76.6 us, 7 parts 67.1).  Without a figure of their own the 128 x 128 tiles seemed half as slow again as they are,
+  // and k = 2048 was split for nothing (2048 x 1228 at 1024 tokens: 43.1 us in 5 parts, 30.0 whole).
+  constexpr double E_PLAIN = 8.0, E_PART = 20.0, SMALL_TILE = 0.55, SMALL_TILES_ONLY = 0.75, SMALLEST_TILES = 0.5, REDUCE_PER_MB = 0.5, REDUCE_FIXED = 6.5;
   auto rounds = [&](int64_t w, bool two_shapes) {
     const int64_t full = w / cus, tail = w % cus;
     if (tail == 0) return (double)full;
     if (two_shapes && full >= 1 && 2 * tail <= cus) return (double)full + SMALL_TILE;   // the last round as 128 x 256 tiles
     return (double)full + 1.0;
   };
-  const double whole = (2 * wgs <= cus ? SMALL_TILES_ONLY : rounds(wgs, true)) * ((double)KB + E_PLAIN);
-  const double part_mb = (double)pl.n_tblocks * 256.0 * (double)pl.n_fblocks * 256.0 * 4.0 / 1.0e6;
+  // (the tiles that a launch without a split takes: launch_prefill_tiles)
+  const bool smallest = 2 * ceil_div(T, (int64_t)128) * pl.n_fblocks <= cus;
+  const double whole = (smallest ? SMALLEST_TILES : 2 * wgs <= cus ? SMALL_TILES_ONLY : rounds(wgs, true)) * ((double)KB + E_PLAIN);
+  const double part_mb = (double)T * (double)pl.n_fblocks * 256.0 * 4.0 / 1.0e6;       // (the rows that the reduce launch reads)
   const int64_t p_max = KB / 8 < SK_MAX_PARTS ? KB / 8 : SK_MAX_PARTS;     // at least 8 pipeline stages per part
-  double best = 0.93 * whole;                                             // a split has to win by 7 %
+  double best = 0.95 * whole;                                             // a split has to win by 5 %
   for (int64_t p = 2; p <= p_max; ++p) {
     const int64_t kbp = ceil_div(KB, p);
     if (ceil_div(KB, kbp) != p) continue;                                  // every part is non-empty

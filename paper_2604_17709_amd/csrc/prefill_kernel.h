@@ -634,7 +634,7 @@ __global__ __launch_bounds__(PF_THREADS) void prefill_kernel(const PfParams P) {
 // One launch with two tile shapes: the first P.n_big workgroups take 256 x 256 tiles of the feature
 // blocks [0, P.fb_shift2), the others 128 x 256 tiles of the remaining feature blocks.  For large
 // launches whose last round of 256 x 256 tiles would leave more than half of the compute units
-// idle: that round's feature blocks run as twice as many smaller tiles, which take about 0.64 of a
+// idle: that round's feature blocks run as twice as many smaller tiles, which take about 0.55 of a
 // large tile's time each.
 template <int DT, bool GLU, int POST, bool ROPE>
 __global__ __launch_bounds__(PF_THREADS) void prefill_mixed_kernel(const PfParams P) {
