@@ -68,6 +68,14 @@ int deinfer_set_decode_glu_one_launch(int mode);
 int deinfer_plan_raw_tile(int64_t M, int64_t N, int64_t K, int dtype, int rows4, int dual, int compute_units, int *tile);
 
 /*
+ * The form that a stage of a call of at most 128 tokens on packed pairs takes on a device of `compute_units` units (host
+ * only): *token_blocks = 0 for the split over k with partial sums, or the number of 32-token blocks (1 or 2) that a
+ * workgroup of the one-launch form multiplies.  blocks: 32-feature blocks of the stage, k_blocks: 32-wide blocks of its k
+ * range, glu: the second stage of a GLU call (features of one of the two products).
+ */
+int deinfer_plan_decode_stage(int64_t T, int64_t blocks, int64_t k_blocks, int glu, int compute_units, int *token_blocks);
+
+/*
  * What this device delivers on the two rooflines of the path (Sec. 5.2 "Throughput Analysis"
  * reports throughput only; the denominators are this build's), for a benchmark that prints a
  * measured ceiling beside the published one.  Both enqueue one kernel on `stream`, allocate

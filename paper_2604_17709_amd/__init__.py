@@ -55,7 +55,7 @@ class DeinferError(RuntimeError):
 EXPORTS = [
     "deinfer_last_error", "deinfer_version", "deinfer_set_profile_events",
     "deinfer_set_prefill_token_tile", "deinfer_set_prefill_feature_tile", "deinfer_set_decode_glu_one_launch",
-    "deinfer_plan_raw_tile",
+    "deinfer_plan_raw_tile", "deinfer_plan_decode_stage",
     "deinfer_rank_for_ratio", "deinfer_probe_stream_read", "deinfer_probe_mfma_bf16",
     "deinfer_packed_bytes", "deinfer_pack_factors",
     "deinfer_workspace_bytes", "deinfer_workspace_init", "deinfer_workspace_check",
@@ -87,6 +87,7 @@ def lib() -> ctypes.CDLL:
         L.deinfer_set_prefill_feature_tile.argtypes = [ctypes.c_int]
         L.deinfer_set_decode_glu_one_launch.argtypes = [ctypes.c_int]
         L.deinfer_plan_raw_tile.argtypes = [_i64, _i64, _i64, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.POINTER(ctypes.c_int)]
+        L.deinfer_plan_decode_stage.argtypes = [_i64, _i64, _i64, ctypes.c_int, ctypes.c_int, ctypes.POINTER(ctypes.c_int)]
         L.deinfer_set_profile_events.argtypes = [ctypes.c_int, _vp, _vp]
         L.deinfer_rank_for_ratio.argtypes = [_i64, _i64, ctypes.c_double, ctypes.POINTER(_i64)]
         L.deinfer_probe_stream_read.argtypes = [_vp, _sz, _vp, _sz, _vp]
@@ -391,6 +392,13 @@ def deinfer_plan_raw_tile(M: int, N: int, K: int, dtype: int, rows4: bool, dual:
     tile = (ctypes.c_int * 3)()
     _check(lib().deinfer_plan_raw_tile(M, N, K, dtype, int(rows4), int(dual), compute_units, tile))
     return tuple(tile)
+
+
+def deinfer_plan_decode_stage(T: int, blocks: int, k_blocks: int, glu: bool, compute_units: int) -> int:
+    """Form of a stage of a call of T <= 128 tokens (host only): 0 split over k, 1 or 2 token blocks per workgroup in one launch."""
+    n = ctypes.c_int(0)
+    _check(lib().deinfer_plan_decode_stage(T, blocks, k_blocks, int(glu), compute_units, ctypes.byref(n)))
+    return n.value
 
 
 def deinfer_set_prefill_feature_tile(features: int) -> None:

@@ -777,6 +777,13 @@ int deinfer_plan_raw_tile(int64_t M, int64_t N, int64_t K, int dtype, int rows4,
   return DEINFER_OK;
 }
 
+int deinfer_plan_decode_stage(int64_t T, int64_t blocks, int64_t k_blocks, int glu, int compute_units, int *token_blocks) {
+  if (T < 1 || T > SKINNY_MAX_T || blocks < 1 || k_blocks < 1 || compute_units < 1 || !token_blocks) return fail(DEINFER_ERR_INVALID_ARG, "decode stage: bad argument");
+  const StChoice c = stream_choice(T, blocks, k_blocks, glu != 0, compute_units);
+  *token_blocks = c.on ? c.NB : 0;
+  return DEINFER_OK;
+}
+
 int deinfer_set_prefill_feature_tile(int features) {
   if (features != 0 && features != 128 && features != 256) return fail(DEINFER_ERR_INVALID_ARG, "feature tile: 0, 128 or 256, got %d", features);
   g_feature_tile = features;

@@ -470,14 +470,21 @@ def test_keys_rebuilt_from_the_low_rank_cache(dn, T):
     assert max_err(to_host(k2), to_host(k).astype(np.float64)) <= 2.0 ** -7    # at most an output rounding apart
 
 
-@pytest.mark.parametrize("T", [9, 17, 33, 64, 65, 97, 128])
-@pytest.mark.parametrize("d_in,r,d_out", [
+# (d_in, r, d_out), with the form of the second stage on 256 compute units (tests/test_plans.py)
+DECODE_STAGE_ROWS = [
     (264, 37, 40),          # one launch per stage, a few workgroups
     (1000, 1021, 200),      # ... k ends inside the last short k-block range
-    (1032, 500, 4100),      # first stage: by the number of workgroups; second: 129 blocks
+    (1032, 500, 4100),      # 129 blocks: from 33 tokens on one or two token blocks per workgroup
     (72, 250, 8200),        # 257 blocks: more than the compute units, left to the split
+    (72, 250, 8100),        # 254 blocks: two token blocks per workgroup, also for the GLU call
     (4200, 1037, 136),      # both stages split over k, with the reduce launch
-])
+    (264, 1500, 3100),      # 97 blocks, long k: one token block per workgroup up to 64 tokens, then two
+    (264, 1900, 4300),      # 135 blocks, long k: two up to 64 tokens, then the split
+]
+
+
+@pytest.mark.parametrize("T", [9, 17, 33, 64, 65, 97, 128])
+@pytest.mark.parametrize("d_in,r,d_out", DECODE_STAGE_ROWS)
 def test_decode_stages_by_token_blocks(dn, T, d_in, r, d_out):
     """Both sides of the choice between one launch of token blocks and the k-split, in both stages, with the
     rank-space output, the GLU form and the upward projection alone on rows that end in NaN."""

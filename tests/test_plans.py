@@ -79,3 +79,39 @@ def test_first_stages_are_split_where_that_was_faster():
     assert first_stage_parts(512, 11008, 1638) >= 10        # 99.7, 55.6 in 16
     assert first_stage_parts(1024, 28672, 3072) in (4, 5)   # 270.9, 184.6 in 4
     assert first_stage_parts(384, 4096, 1228) >= 8          # 47.8, 40.0 in 16
+
+
+def stage(k, features, T, glu=False):
+    return dn.deinfer_plan_decode_stage(T, -(-features // 32), -(-k // 32), glu, CUS)
+
+
+def test_form_of_measured_decode_stages():
+    """Stages that were timed in every form (us: split / one / two token blocks per workgroup)."""
+    # 33 .. 64 tokens, just above 128 blocks: one round of two-block workgroups
+    for k, f, T in ((1024, 4128, 48), (1024, 4480, 64), (2048, 4128, 64), (2048, 4480, 48), (1240, 4128, 40), (1240, 4480, 40)):
+        assert stage(k, f, T) == 2                      # 2048 x 4480, 64 tokens: 14.4 / 14.4 / 13.1; 1240 x 4480, 40: 11.6 / 13.6 / 9.9
+    assert stage(1640, 4128, 64) == 0                   # 13.4 / 15.6 / 14.0
+    assert stage(256, 8192, 64) == 2                    # 11.8 / 7.1 / 5.8
+    assert stage(1640, 4096, 128) == 2                  # 17.9 / 15.1 / 13.5
+    assert stage(1024, 8192, 128) == 2                  # 18.4 / 15.5 / 13.9
+    assert stage(512, 4096, 64) == 1                    # 12.1 / 5.7 / 6.2
+    assert stage(1024, 4480, 128) == 1                  # 17.7 / 11.8 / 13.1
+    assert stage(1640, 1024, 128) == 1                  # 11.5 / 8.7 / 12.4
+    assert stage(4096, 2048, 128) == 1                  # 14.9 / 12.9 / 19.5
+    # a last token block that is nearly empty
+    assert stage(4096, 3072, 40) == 0                   # 13.2 / 14.1 / 17.2
+    for k, f in ((1640, 2048), (1640, 3072), (1800, 2560), (2560, 2048), (2560, 3072)):
+        assert stage(k, f, 40, glu=True) == 0           # 1640 x 3072: 12.8 / 14.7 / 16.4
+    # GLU
+    assert stage(512, 3584, 64, glu=True) == 1          # 12.4 / 6.3 / 8.2
+    assert stage(512, 3584, 128, glu=True) == 2         # 17.4 / 8.8 / 8.1
+    assert stage(1024, 4480, 64, glu=True) == 2         # 14.0 / 13.6 / 12.2
+    assert stage(1640, 2048, 128, glu=True) == 1        # 18.2 / 13.5 / 20.4
+    assert stage(2560, 2048, 128, glu=True) == 1        # 19.3 / 16.5 / 26.6
+    assert stage(1024, 6000, 96, glu=True) == 0         # 16.6 / 18.0 / 19.7
+
+
+def test_every_form_of_a_decode_stage_is_taken_by_the_rows_of_its_test():
+    from test_gpu_parity import DECODE_STAGE_ROWS
+    forms = {(glu, stage(r, d_out, T, glu), T > 64) for T in (9, 17, 33, 64, 65, 97, 128) for _, r, d_out in DECODE_STAGE_ROWS for glu in (False, True)}
+    assert forms >= {(g, f, late) for g in (False, True) for f in (0, 1, 2) for late in (False, True)}
