@@ -450,7 +450,7 @@ def main():
         torch.cuda.synchronize()
         gemm_pad_us = events_us(lambda i: torch.matmul(gap, gbp, out=gc), 20)
         roofline["measured_ceiling"] = {
-            "what": "deinfer_probe_mfma_bf16: back-to-back 32x32x16 bf16 products on register operands (activation values), "
+            "what": "deinfer_probe_mfma_bf16: back-to-back 16x16x32 bf16 products on register operands (activation values), "
                     "one wavefront per SIMD, no memory traffic",
             "products_only_TFLOPs": round(fl[0] / mf_us / 1e6, 1),
             "frac_of_products_only": round(ach / (fl[0] / mf_us / 1e6), 4),

@@ -84,7 +84,7 @@ int deinfer_plan_decode_stage(int64_t T, int64_t blocks, int64_t k_blocks, int g
  *   deinfer_probe_stream_read  reads buf[0 .. bytes) once (bytes a positive multiple of 1024,
  *                              buf 16-byte aligned, device) with plain coalesced loads.
  *   deinfer_probe_mfma_bf16    every wavefront of a one-workgroup-per-compute-unit grid issues
- *                              8 * n_rounds bf16 32x32x16 matrix products back to back on register
+ *                              16 * n_rounds bf16 16x16x32 matrix products back to back on register
  *                              operands taken from `operands` (device, >= 8192 bytes of bf16
  *                              values, 16-byte aligned); *flops_out (host, may be NULL) receives
  *                              the floating-point operations of the launch.

@@ -127,8 +127,9 @@ template <int DT> __device__ __forceinline__ f32x4_t mfma16(const u32x4_t &a, co
 // c += a . b with the accumulator held in the accumulation registers by constraint: with 64 accumulator
 // blocks of four registers per lane the compiler otherwise keeps part of them in ordinary registers and
 // moves them back and forth in the loop.  The hazard between the last product and the first read of a sum
-// is the caller's: mfma_settle before the sums are used.  The operands must come from memory or LDS (an
-// ordinary vector instruction that writes one needs two wait states before the product reads it).
+// is the caller's: mfma_settle before the sums are used.  The operands must come from memory or LDS, and sums that
+// an ordinary vector instruction has written (the zeros of the start) need two wait states before the product
+// reads them.  tests/test_kernel_code.py checks the built kernels for both.
 template <int DT> __device__ __forceinline__ void mfma16_acc(const u32x4_t &a, const u32x4_t &b, f32x4_t &c) {
 #if defined(__HIP_DEVICE_COMPILE__)
   if constexpr (DT == DT_F16) asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));

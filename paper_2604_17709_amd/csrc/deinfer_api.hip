@@ -816,8 +816,8 @@ int deinfer_probe_mfma_bf16(const void *operands, size_t operand_bytes, int64_t 
     return fail(DEINFER_ERR_WORKSPACE, "probe: sink smaller than DEINFER_PROBE_SINK_BYTES");
   hipLaunchKernelGGL(probe_mfma_bf16_kernel, dim3((unsigned)cus), dim3(PROBE_MFMA_THREADS), 0, static_cast<hipStream_t>(stream),
                      static_cast<const u32x4_t *>(operands), (int)n_rounds, static_cast<float *>(sink));
-  if (flops_out)      // 32 x 32 x 16 multiply-adds per product
-    *flops_out = 2.0 * 32 * 32 * 16 * (double)PROBE_MFMA_ACC * (double)n_rounds * (PROBE_MFMA_THREADS / 64) * (double)cus;
+  if (flops_out)      // 16 x 16 x 32 multiply-adds per product
+    *flops_out = 2.0 * 16 * 16 * 32 * (double)PROBE_MFMA_ACC * (double)n_rounds * (PROBE_MFMA_THREADS / 64) * (double)cus;
   return check_launch("MFMA probe");
 }
 

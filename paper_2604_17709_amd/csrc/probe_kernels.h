@@ -2,10 +2,10 @@
 // against, so that a benchmark can print a measured denominator beside the published one.
 //   probe_stream_read_kernel   plain coalesced read of a buffer (16 bytes per lane, eight loads in
 //                              flight per lane, nontemporal), nothing done with the data
-//   probe_mfma_bf16_kernel     back-to-back 32x32x16 bf16 products on register operands (one
-//                              wavefront per SIMD, eight independent accumulator blocks), no memory
-//                              traffic inside the loop; the operands come from a caller buffer, so
-//                              the switching activity is that of real values
+//   probe_mfma_bf16_kernel     back-to-back 16x16x32 bf16 products, the instruction of the compute-bound kernel, on
+//                              register operands (one wavefront per SIMD, sixteen independent accumulator
+//                              blocks), no memory traffic inside the loop; the operands come from a caller
+//                              buffer, so the switching activity is that of real values
 #pragma once
 #include "common.h"
 
@@ -14,7 +14,7 @@ namespace deinfer {
 constexpr int PROBE_READ_THREADS = 512;
 constexpr int PROBE_READ_UNROLL = 8;
 constexpr int PROBE_MFMA_THREADS = 256;
-constexpr int PROBE_MFMA_ACC = 8;
+constexpr int PROBE_MFMA_ACC = 16;
 
 // n_kb: 1 KiB pieces (64 lanes x 16 bytes).  Workgroup g takes pieces [g n_kb / G, (g + 1) n_kb / G).
 __global__ __launch_bounds__(PROBE_READ_THREADS) void probe_stream_read_kernel(const u32x4_t *src, size_t n_kb, u32x4_t *sink) {
@@ -39,22 +39,26 @@ __global__ __launch_bounds__(PROBE_READ_THREADS) void probe_stream_read_kernel(c
 // Every wavefront issues n_rounds * PROBE_MFMA_ACC products.  operands: 256 x 32 bytes of bf16.
 __global__ __launch_bounds__(PROBE_MFMA_THREADS) void probe_mfma_bf16_kernel(const u32x4_t *operands, int n_rounds, float *sink) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  f32x16_t acc[PROBE_MFMA_ACC];
+  f32x4_t acc[1][PROBE_MFMA_ACC];
 #pragma unroll
-  for (int i = 0; i < PROBE_MFMA_ACC; ++i)
+  for (int i = 0; i < PROBE_MFMA_ACC; ++i) {
 #pragma unroll
-    for (int e = 0; e < 16; ++e) acc[i][e] = 0.f;
+    for (int e = 0; e < 4; ++e) acc[0][i][e] = 0.f;
+    asm volatile("" : "+a"(acc[0][i]));
+  }
   const u32x4_t a = operands[2 * threadIdx.x], b = operands[2 * threadIdx.x + 1];
+  asm volatile("s_nop 7");                             // (the zeros are written: see mfma16_acc)
+#pragma unroll 8                                         // (a loop of 16 products alone loses 5 % to its branch)
   for (int it = 0; it < n_rounds; ++it) {
 #pragma unroll
-    for (int i = 0; i < PROBE_MFMA_ACC; ++i)
-      acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(a), as_bf16x8(b), acc[i], 0, 0, 0);
+    for (int i = 0; i < PROBE_MFMA_ACC; ++i) mfma16_acc<DT_BF16>(a, b, acc[0][i]);
   }
+  mfma_settle(acc);
   float s = 0.f;
 #pragma unroll
   for (int i = 0; i < PROBE_MFMA_ACC; ++i)
 #pragma unroll
-    for (int e = 0; e < 16; ++e) s += acc[i][e];
+    for (int e = 0; e < 4; ++e) s += acc[0][i][e];
   sink[(size_t)blockIdx.x * PROBE_MFMA_THREADS + threadIdx.x] = s;
 #else
   (void)operands; (void)n_rounds; (void)sink;

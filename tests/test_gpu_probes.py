@@ -15,7 +15,8 @@ def test_mfma_probe_counts_its_products():
     torch.cuda.synchronize()
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     assert flops == 2.0 * 32 * 32 * 16 * 8 * n * 4 * cus
-    # every element of every accumulator block is 16 * n; a lane sums 8 blocks x 16 elements
+    # sixteen blocks of 16x16x32 products: every element is 32 * n and a lane sums 16 blocks x 4 elements, which is the
+    # same number of operations and the same sum as of eight blocks of 32x32x16
     got = sink[: cus * 256]
     assert torch.all(got == 8 * 16 * 16.0 * n)
     assert torch.all(sink[cus * 256:] == 0)

@@ -13,7 +13,7 @@ import paper_2604_17709_amd as dn
 LLVM = "/opt/rocm/llvm/bin"
 TOOLS = {t: os.path.join(LLVM, t) for t in ("llvm-objcopy", "clang-offload-bundler", "llvm-objdump", "llvm-readobj")}
 
-# Wait states between a vector instruction that writes an operand of a matrix product and the product, and between a
+# Wait states between a vector instruction that writes an operand or a sum of a matrix product and the product, and between a
 # product of eight passes (16x16x32) and another use of its result.
 OPERAND_WAIT, RESULT_WAIT = 2, 11
 
@@ -77,7 +77,7 @@ def hazards(lines):
     for i0, (_, op, ops, _) in enumerate(code):
         if op.startswith("v_mfma") and ops[0].startswith("a"):
             products += 1
-            need = registers(ops[1]) | registers(ops[2])
+            need = registers(ops[1]) | registers(ops[2]) | registers(ops[3])
             walk(i0, OPERAND_WAIT, lambda j: code[j][1].startswith("v_") and not code[j][1].startswith(("v_mfma", "v_cmp", "v_readfirstlane", "v_readlane"))
                  and bool(registers(code[j][2][0]) & need))
         else:
@@ -120,7 +120,7 @@ def test_products_on_accumulation_registers_have_no_hazard(device_code):
 
     def check():
         nonlocal kernels, products
-        if "prefill" in name:
+        if name and ("prefill" in name or "probe_mfma" in name):
             n, found = hazards(lines)
             assert not found, (name, found[:5])
             kernels, products = kernels + 1, products + n
@@ -129,7 +129,7 @@ def test_products_on_accumulation_registers_have_no_hazard(device_code):
         if line.endswith(">:\n"):
             check()
             name, lines = line, []
-        elif "prefill" in name:
+        elif "prefill" in name or "probe_mfma" in name:
             lines.append(line)
     check()
     assert proc.wait() == 0
@@ -149,6 +149,7 @@ def test_the_hazard_check_finds_planted_hazards():
         assert len(hazards(listing(write, "s_mov_b32 s0, 0", mfma))[1]) == 1
         assert hazards(listing(write, "s_nop 1", mfma))[1] == []
     assert hazards(listing("v_mov_b32_e32 v7, v1", mfma))[1] == []
+    assert len(hazards(listing("v_accvgpr_write_b32 a1, 0", mfma))[1]) == 1
     assert len(hazards(listing(mfma, "s_nop 9", read))[1]) == 1
     assert hazards(listing(mfma, "s_nop 15", "s_nop 15", read))[1] == []
     # round a loop: the write at its end, the product at its start
