@@ -22,7 +22,7 @@ struct BufOffsets { unsigned lane, scalar; };
 // the descriptor's size LESS the scalar offset, and a scalar offset beyond the size would make that difference
 // wrap: a dead load therefore takes the scalar offset 0.
 DEINFER_HOST_DEVICE BufOffsets weight_load(bool live, unsigned lane, unsigned scalar) {
-  return live ? BufOffsets{lane, scalar} : BufOffsets{BUF_DEAD, 0u};
+  return BufOffsets{lane | (live ? 0u : BUF_DEAD), live ? scalar : 0u};      // (two scalar selects and one vector instruction)
 }
 
 }  // namespace deinfer
