@@ -48,11 +48,16 @@ __global__ __launch_bounds__(PROBE_MFMA_THREADS) void probe_mfma_bf16_kernel(con
   }
   const u32x4_t a = operands[2 * threadIdx.x], b = operands[2 * threadIdx.x + 1];
   asm volatile("s_nop 7");                             // (the zeros are written: see mfma16_acc)
-#pragma unroll 8                                         // (a loop of 16 products alone loses 5 % to its branch)
-  for (int it = 0; it < n_rounds; ++it) {
+  auto round = [&] {
 #pragma unroll
     for (int i = 0; i < PROBE_MFMA_ACC; ++i) mfma16_acc<DT_BF16>(a, b, acc[0][i]);
+  };
+  int it = 0;                                          // (eight rounds to a branch: 5 % more products than one)
+  for (; it + 8 <= n_rounds; it += 8) {
+#pragma unroll
+    for (int r = 0; r < 8; ++r) round();
   }
+  for (; it < n_rounds; ++it) round();
   mfma_settle(acc);
   float s = 0.f;
 #pragma unroll
