@@ -22,10 +22,12 @@
 // weight fragments are already contiguous 1 KiB pieces; activations come as 128-byte token rows,
 // the two k-blocks of a pair of stages at once, whose eight 16-byte slots are XOR-swizzled with
 // (row / 2) % 8, applied on the global side of the load (lane -> slot is fixed, lane -> k-chunk is
-// permuted), which keeps the operand reads free of bank conflicts without padding.
+// permuted), which keeps the operand reads free of bank conflicts without padding (SQ_LDS_BANK_CONFLICT is 0 in the
+// k-split launches, which use LDS for nothing else; the epilogue's transpose costs the others 1-8 % of their LDS cycles).
 // What bounds the loop beside the products is the number of requests to L2.  One k-block per row
 // and load (64 bytes, half a cache line) made every row two requests: 384 per 256 x 256 tile and
-// stage, by TCP_TCC_READ_REQ; whole lines make it 256.  7B block, 512 tokens 295 -> 271 us (its GLU
+// stage; whole lines make it 256 (70B GLU launch: TCP_TCC_READ_REQ_sum 73.4 M over 1792 tiles of 160
+// stages).  7B block, 512 tokens 295 -> 271 us (its GLU
 // launch 70 -> 61 us), 8192 tokens 1749 -> 1627 us; 70B at 4096 tokens 2426 -> 2321 us; 13B at 8256
 // 2820 -> 2740 us; cached keys and values of 8192 tokens 243 -> 230 us.  (Rows whose pitch or first
 // column is no multiple of 128 bytes keep part of the second requests.)
@@ -53,8 +55,8 @@ constexpr int PF_BT = 256;                 // tokens per workgroup tile
 constexpr int PF_BK = 32;                  // k per pipeline stage (one k-block)
 constexpr int PF_STAGES = 4;               // LDS stage buffers of the 256-token tile
 constexpr int PF_STAGES_TB2 = 6;           // ... of the 128 x 256 tile (half the products per stage: a deeper queue for the same cover)
-constexpr int PF_STAGES_MF4 = 6;           // ... of the 128 x 128 tile (four stages, which would let two workgroups share a
-                                           // compute unit, measured 3-7 % slower on launches of 32-128 tiles; eight the same as six)
+constexpr int PF_STAGES_MF4 = 6;           // ... of the 128 x 128 tile (blocks of 200 to 1024 tokens, where both small tiles run,
+                                           // are 7-14 % slower with four stages for both, 1-4 % slower with eight for this one)
 constexpr int pf_stages(int tb, int mf = 8) { return tb == 4 ? PF_STAGES : mf == 8 ? PF_STAGES_TB2 : PF_STAGES_MF4; }
 
 // Launches with at most this many token blocks give every XCD (workgroup index mod 8) a contiguous run of tiles:
@@ -127,8 +129,8 @@ struct PfShared {
 // feature i of a head pairs with feature i + 64 of the same token, both in this wavefront's LDS
 // tile), on the rounded products, cos / sin from a table; the result is rounded once more.
 // TB = 32-token blocks per wavefront: 4 (workgroup tile of 256 tokens) or 2 (128 tokens: twice the
-// workgroups, for launches whose 256-token tiles are fewer than the compute units; its loop keeps a
-// whole k-step of operands ahead instead of the hand-placed reads of the TB = 4 loop).
+// workgroups, for launches whose 256-token tiles are fewer than the compute units; the same stage schedule with
+// half the groups and a deeper queue).
 // The body of a workgroup: bid = its index among the workgroups of this tile shape, n_tblocks = token
 // blocks of this tile shape, fb_shift = first feature block of this tile shape (0 unless the launch
 // mixes two shapes, see prefill_mixed_kernel).

@@ -5,10 +5,11 @@
 //
 // One workgroup = one block of 32 features (and of 32 NB tokens); its four wavefronts split the k range of that block
 // ("split-r reduction through LDS"): each streams its quarter of the block's weights straight into
-// registers (non-temporal, every byte is used once) and keeps its own [T x 64 k] activation slabs
+// registers (non-temporal: a workgroup uses every byte once, the workgroups of a feature block's token blocks
+// read it one beside the other) and keeps its own [32 NB x 64 k / NB] activation slabs
 // in its own LDS region (global -> LDS loads, 64-byte rows with XOR-swizzled 16-byte slots).
 // Nothing is shared between the wavefronts until the end, so there is no barrier in the loop; a
-// wavefront waits only for its own loads.  Four slots (64 k each at T <= 32, 32 k at T <= 64) are in
+// wavefront waits only for its own loads.  Four slots (64 k each with NB = 1, 32 k with NB = 2) are in
 // flight per wavefront; two workgroups share a compute unit (64 KiB of LDS each).
 // The four accumulator sets are added through LDS and the epilogue (bf16 rounding, optional second
 // copy of t, SiLU-GLU) writes the final output.  For the GLU call the workgroup owns 32 output
@@ -17,8 +18,9 @@
 // More tokens than a workgroup holds are further workgroups (StParams::n_tblocks): short stages, where the
 // loads of a whole wavefront's k range are a few round trips, gain more from one launch without partial
 // sums than the weights' second and fourth reading (from the XCD's L2) costs.  One upward projection at
-// 128 tokens against split + reduce: 1024 features, k = 512: 9.7 -> 5.3 us, k = 1640: 11.7 -> 9.1 us; 8192
-// features, k = 1024: 18.5 -> 15.4 us (k = 1640: 21.2 -> 26.8 us, left to the split).
+// 128 tokens against split + reduce, weights from HBM: 1024 features, k = 1640: 11.5 -> 8.7 us; 4096 features, k = 1640
+// with NB = 2: 17.9 -> 13.5 us; 8192 features, k = 1024 with NB = 2: 18.4 -> 13.9 us (stream_choice in
+// skinny_host.inc has the ranges).
 #pragma once
 #include "common.h"
 #include "skinny_kernel.h"
