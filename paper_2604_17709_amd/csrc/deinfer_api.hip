@@ -197,7 +197,8 @@ struct PfSplitPlan {
   int n_parts, kb_per_part, n_fblocks, n_tblocks;
   size_t part_bytes;          // 0: no split
 };
-PfSplitPlan prefill_split_plan(int64_t T, const deinfer_factors_t *const *f, int n) {
+// (limit: bytes of scratch that the call may use at most, for the entry point whose scratch is a fixed array)
+PfSplitPlan prefill_split_plan(int64_t T, const deinfer_factors_t *const *f, int n, size_t limit) {
   PfSplitPlan pl;
   memset(&pl, 0, sizeof(pl));
   int64_t tiles = 0;
@@ -235,6 +236,8 @@ PfSplitPlan prefill_split_plan(int64_t T, const deinfer_factors_t *const *f, int
   for (int64_t p = 2; p <= p_max; ++p) {
     const int64_t kbp = ceil_div(KB, p);
     if (ceil_div(KB, kbp) != p) continue;                                  // every part is non-empty
+    const size_t scratch = (size_t)round_up((int64_t)(round_up(T, 256) * tiles * 16 * 2), 256) + (size_t)p * pl.n_tblocks * 256 * (size_t)pl.n_fblocks * 256 * sizeof(float);
+    if (scratch > limit - WS_HEADER) continue;
     const double est = rounds(wgs * p, false) * ((double)kbp + E_PART) + (double)p * part_mb * REDUCE_PER_MB + REDUCE_FIXED;
     if (est < best) { best = est; pl.n_parts = (int)p; pl.kb_per_part = (int)kbp; }
   }
@@ -270,7 +273,7 @@ int validate_pair(const deinfer_factors_t *f, const char *name) {
   return DEINFER_OK;
 }
 
-size_t workspace_need_of(int64_t T, const deinfer_factors_t *const *pairs, int n) {
+size_t workspace_need_of(int64_t T, const deinfer_factors_t *const *pairs, int n, size_t limit) {
   int64_t rtot = 0, rtot_pad = 0;
   for (int i = 0; i < n; ++i) { rtot += pairs[i]->r; rtot_pad += round_up(pairs[i]->r, 32); }
   const bool packed = pairs[0]->layout == DEINFER_LAYOUT_PACKED;
@@ -282,7 +285,7 @@ size_t workspace_need_of(int64_t T, const deinfer_factors_t *const *pairs, int n
     // T <= 16: t in fragment order and up to DEC_MAX_PARTS fp32 part buffers of one 16-token tile
     const size_t tdec = T <= 16 ? (size_t)round_up((int64_t)16 * rp * 2, 256) + (size_t)DEC_MAX_PARTS * 16 * rp * 4 : 0;
     size_t tpre = T > SKINNY_MAX_T ? (size_t)round_up(T, 256) * rp * 2 : 0;
-    if (T > SKINNY_MAX_T) tpre = (size_t)round_up((int64_t)tpre, 256) + prefill_split_plan(T, pairs, n).part_bytes;
+    if (T > SKINNY_MAX_T) tpre = (size_t)round_up((int64_t)tpre, 256) + prefill_split_plan(T, pairs, n, limit).part_bytes;
     scratch = round_up((int64_t)tdec, 256) + round_up((int64_t)tpre, 256);
     if (T <= SKINNY_MAX_T) { // (the upward-projection-only call uses this schedule for every such T)
       for (int glu = 0; glu < 2; ++glu) {      // (the call is not known here: room for either kind)
@@ -298,14 +301,15 @@ size_t workspace_need_of(int64_t T, const deinfer_factors_t *const *pairs, int n
 // Bytes that a call with these pairs may use.  Pairs of rank 0 are dropped before the dispatch (their
 // outputs are zero-filled), and the remaining group may split differently (fewer feature groups admit
 // more k-ranges, i.e. more partial sums): room for the group as given and for the group that runs.
-size_t workspace_need(int64_t T, const deinfer_factors_t *const *pairs, int n) {
-  size_t need = workspace_need_of(T, pairs, n);
+constexpr size_t NO_LIMIT = ~(size_t)0;
+size_t workspace_need(int64_t T, const deinfer_factors_t *const *pairs, int n, size_t limit = NO_LIMIT) {
+  size_t need = workspace_need_of(T, pairs, n, limit);
   const deinfer_factors_t *rest[3];
   int m = 0;
   for (int i = 0; i < n && i < 3; ++i)
     if (pairs[i]->r > 0) rest[m++] = pairs[i];
   if (m > 0 && m < n) {
-    const size_t reduced = workspace_need_of(T, rest, m);
+    const size_t reduced = workspace_need_of(T, rest, m, limit);
     if (reduced > need) need = reduced;
   }
   return need;
@@ -340,6 +344,7 @@ struct Group {
   const void *x2; int64_t ldx2;            // up_only GLU call: rank-space rows of the second (up) pair
   const float *rope; int64_t rope_dim;     // single up_only pair: rotary embedding of the output from a [T][rope_dim] cos | sin table
   void *ws; size_t ws_bytes; hipStream_t stream;
+  bool fixed_scratch;                      // the workspace is the static array: a plan that fits it, not the best plan
 };
 
 template <int DT, int NT>
@@ -600,7 +605,7 @@ int run_group(Group gq) {
     }
   if (!gq.ws) return fail(DEINFER_ERR_WORKSPACE, "workspace pointer is NULL");
   if (!aligned(gq.ws, 256)) return fail(DEINFER_ERR_MISALIGNED, "workspace must be 256-byte aligned");
-  const size_t need = workspace_need(gq.T, gq.f, gq.n);
+  const size_t need = workspace_need(gq.T, gq.f, gq.n, gq.fixed_scratch ? gq.ws_bytes : NO_LIMIT);
   if (gq.ws_bytes < need)
     return fail(DEINFER_ERR_WORKSPACE, "workspace too small: %zu bytes given, %zu needed", gq.ws_bytes, need);
   const bool packed = gq.f[0]->layout == DEINFER_LAYOUT_PACKED;
@@ -1056,14 +1061,18 @@ int deinfer_lowrank_linear_static(const void *x, int64_t T, int64_t ldx, const d
   if (int rc = validate_pair(f, "pair 0")) return rc;
   if (T < 0) return fail(DEINFER_ERR_INVALID_ARG, "T is negative");
   const deinfer_factors_t *pairs[1] = {f};
-  const size_t need = workspace_need(T, pairs, 1);
+  const size_t need = workspace_need(T, pairs, 1, (size_t)DEINFER_STATIC_SCRATCH_BYTES);
   if (need > (size_t)DEINFER_STATIC_SCRATCH_BYTES)
     return fail(DEINFER_ERR_WORKSPACE, "this call needs %zu bytes of scratch, the static scratch array holds %zu: "
                 "use deinfer_lowrank_linear with a workspace of the caller's", need, (size_t)DEINFER_STATIC_SCRATCH_BYTES);
   void *ws = nullptr;                    // (T == 0 returns before the workspace is looked at)
   if (T > 0)
     if (int rc = static_scratch(&ws)) return rc;
-  return deinfer_lowrank_linear(x, T, ldx, f, y, ldy, ws, (size_t)DEINFER_STATIC_SCRATCH_BYTES, stream);
+  Group g;
+  memset(&g, 0, sizeof(g));
+  g.x = x; g.T = T; g.ldx = ldx; g.n = 1; g.f[0] = f; g.out[0] = y; g.ldo[0] = ldy;
+  g.ws = ws; g.ws_bytes = (size_t)DEINFER_STATIC_SCRATCH_BYTES; g.fixed_scratch = true; g.stream = static_cast<hipStream_t>(stream);
+  return run_group(g);
 }
 
 int deinfer_lowrank_up(const void *t, int64_t T, int64_t ldt, const deinfer_factors_t *f,

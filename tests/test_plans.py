@@ -1,4 +1,5 @@
 """The choices of the host code (which tile, which form of a stage), asked through the testing header: no device."""
+import ctypes
 import itertools
 import random
 import types
@@ -115,3 +116,16 @@ def test_every_form_of_a_decode_stage_is_taken_by_the_rows_of_its_test():
     from test_gpu_parity import DECODE_STAGE_ROWS
     forms = {(glu, stage(r, d_out, T, glu), T > 64) for T in (9, 17, 33, 64, 65, 97, 128) for _, r, d_out in DECODE_STAGE_ROWS for glu in (False, True)}
     assert forms >= {(g, f, late) for g in (False, True) for f in (0, 1, 2) for late in (False, True)}
+
+
+def test_the_static_scratch_entry_takes_a_split_that_fits():
+    """First stages whose best split needs more than the static array, while a smaller one (or none) fits it: not refused for
+    lack of scratch (without a device the call then fails for that reason, with one it is not made here)."""
+    if torch.cuda.is_available():
+        pytest.skip("the pointers are not real")
+    for T, d_in, r in ((375, 5608, 1249), (142, 3040, 3040), (131, 3560, 3560), (519, 5688, 522)):
+        f = dn.Factors()
+        f.U, f.V, f.d_in, f.d_out, f.r, f.dtype, f.layout = 1 << 28, 1 << 29, d_in, 64, r, dn.BF16, dn.LAYOUT_PACKED
+        assert dn.deinfer_workspace_bytes(T, [types.SimpleNamespace(desc=f)]) > dn.STATIC_SCRATCH_BYTES
+        rc = dn.lib().deinfer_lowrank_linear_static(1 << 30, T, d_in, ctypes.byref(f), 1 << 31, 64, None)
+        assert rc == dn.ERR_DEVICE, dn.last_error()

@@ -49,6 +49,22 @@ def _both(dn, seed, T, d_in, r, d_out):
     return p, keep
 
 
+def test_static_scratch_entry_point_takes_a_split_that_fits(dn):
+    """A first stage whose best split needs more than the static array runs with fewer partial sums."""
+    import torch
+    T, d_in, r, d_out = 142, 3040, 3040, 64
+    x = si.make(55, 1, (T, d_in), 1.0, "bf16")
+    U = si.make(55, 2, (d_in, r), 1.0 / np.sqrt(d_in), "bf16")
+    V = si.make(55, 3, (r, d_out), 1.0 / np.sqrt(r), "bf16")
+    p, keep = pair(dn, U, V, packed=True)
+    xd = to_dev(x)
+    y = torch.full((T, d_out), 7.0, dtype=torch.bfloat16, device="cuda")
+    rc = dn.lib().deinfer_lowrank_linear_static(xd.data_ptr(), T, xd.stride(0), ctypes.byref(p.desc), y.data_ptr(), y.stride(0), None)
+    assert rc == dn.OK, dn.last_error()
+    torch.cuda.synchronize()
+    assert max_err(to_host(y), oracle.lowrank_linear(x.values, U.values, V.values)) <= TOL["bf16"]
+
+
 def test_static_scratch_entry_point_matches_the_workspace_one(dn):
     import torch
     # every schedule: T <= 8 (tile kernels), <= 32 / <= 128 (streaming kernels with partial sums), > 128 (large tiles with a k-split)
