@@ -167,10 +167,11 @@ int deinfer_lowrank_gateup_silu(const void *x, int64_t T, int64_t ldx,
  * up.  Limits: calls that cannot run in DEINFER_STATIC_SCRATCH_BYTES return DEINFER_ERR_WORKSPACE and
  * enqueue nothing (decode-sized calls up to the 70B shapes at 128 tokens fit; every call whose
  * deinfer_workspace_bytes is no larger does; a larger call of more than 128 tokens may run with fewer
- * partial sums than deinfer_lowrank_linear would take, and then differs from it by rounding).  Every call on one GPU uses that GPU's one array: calls that overlap in time on one GPU
- * (different streams, or graphs replayed concurrently) race; serialise them or use
- * deinfer_lowrank_linear with separate workspaces.  Nothing in the array has to survive between
- * calls and nothing has to be cleared.  Otherwise the contract of deinfer_lowrank_linear.
+ * partial sums than deinfer_lowrank_linear would take, and then differs from it by rounding).  Every
+ * call on one GPU uses that GPU's one array: calls that overlap in time on one GPU (different
+ * streams, or graphs replayed concurrently) race; serialise them or use deinfer_lowrank_linear with
+ * separate workspaces.  Nothing in the array has to survive between calls and nothing has to be
+ * cleared.  Otherwise the contract of deinfer_lowrank_linear.
  */
 #define DEINFER_STATIC_SCRATCH_BYTES (32u << 20)
 int deinfer_lowrank_linear_static(const void *x, int64_t T, int64_t ldx, const deinfer_factors_t *f,

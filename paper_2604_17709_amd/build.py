@@ -2,8 +2,7 @@
 
     python -m paper_2604_17709_amd.build          # compile libdeinfer.so next to this file
 
-The shared object is built in-tree so that it travels with the source snapshot to the
-GPU machine; nothing is compiled at import time.
+The shared object is built in-tree, beside its sources; nothing is compiled at import time.
 """
 from __future__ import annotations
 
