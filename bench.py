@@ -387,13 +387,11 @@ def main():
         ach = kflops[kdom] / ksec / 1e12
         roofline = {"bound": "mfma", "achieved": round(ach, 1), "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
                     "frac": round(ach / MFMA_BF16_PEAK_TFLOPS, 4), "traffic": traffic}
-    # (which kernel a launch is: the tile kernels up to 8 tokens, the streaming kernels up to 128 - for the
-    # GLU call's second stage skinny_glu_kernel where its workgroups fill most of the device, else
-    # skinny_kernel / stream_kernel -, prefill_kernel beyond; the rocprofv3 summaries under profiles/ name it)
+    # (which kernel a launch is: the tile kernels up to 8 tokens, the streaming kernels up to 128,
+    # prefill_kernel beyond; the rocprofv3 summaries under profiles/ name it)
     tiles16 = lambda n: (n + 15) // 16
     small = (T <= 8 and sum(tiles16(ranks[p]) for p in ps) <= 256 and sum(tiles16(proj[p][1]) for p in ps) <= 1024)
-    kname = ("decode_kernel" if small else "skinny_glu_kernel / skinny_kernel" if (dom == "gateup" and shape.glu and kdom == "up" and T > 16)
-             else "skinny_kernel / stream_kernel") if decode else "prefill_kernel"
+    kname = ("decode_kernel" if small else "skinny_kernel / stream_kernel") if decode else "prefill_kernel"
     roofline["kernel"] = "%s (%s-projection launch of deinfer_lowrank_%s)" % (kname, kdom, entry)
     roofline["traffic_source"] = traffic_source
     roofline["avg_launch_us"] = round(ksec * 1e6, 2)

@@ -61,6 +61,14 @@ int deinfer_set_prefill_feature_tile(int features);
 int deinfer_set_decode_glu_one_launch(int mode);
 
 /*
+ * The second stage of a call of at most 128 tokens on packed pairs, for the calls of THIS THREAD (those that do not take
+ * the kernels of 8 tokens and fewer): 0 (the default) lets every call choose; -1 never as tiles over the whole k range;
+ * 100 NB + 10 NW + KH forces tiles of 32 NB tokens x 32 NW features with KH parts of the k range side by side in a
+ * workgroup (a form that is not built makes the call return DEINFER_ERR_UNSUPPORTED).
+ */
+int deinfer_set_decode_tile(int form);
+
+/*
  * The choice that a call on RAW pairs makes for one product [M x K] . [K x N] on a device of `compute_units` units
  * (host only): tile[0] x tile[1] = rows x columns of a workgroup's tile, tile[2] = its wavefronts.  rows4: the rows of
  * the second operand are aligned to four elements; dual: the product pair of a GLU call (K: the mean of the two).
@@ -74,6 +82,13 @@ int deinfer_plan_raw_tile(int64_t M, int64_t N, int64_t K, int dtype, int rows4,
  * range, glu: the second stage of a GLU call (features of one of the two products).
  */
 int deinfer_plan_decode_stage(int64_t T, int64_t blocks, int64_t k_blocks, int glu, int compute_units, int *token_blocks);
+
+/*
+ * Whether the second stage of such a call runs as tiles over the whole k range instead (host only): tile[0] x tile[1] =
+ * tokens x features of a workgroup, tile[2] = parts of the k range inside it; tile[0] = 0: the other forms.  features: of
+ * the n products of the call (glu: n = 1, of one of the two), k_blocks: the longest k range.
+ */
+int deinfer_plan_decode_tile(int64_t T, const int64_t *features, int n, int64_t k_blocks, int glu, int compute_units, int *tile);
 
 /*
  * What this device delivers on the two rooflines of the path (Sec. 5.2 "Throughput Analysis"

@@ -55,6 +55,7 @@ class DeinferError(RuntimeError):
 EXPORTS = [
     "deinfer_last_error", "deinfer_version", "deinfer_set_profile_events",
     "deinfer_set_prefill_token_tile", "deinfer_set_prefill_feature_tile", "deinfer_set_decode_glu_one_launch",
+    "deinfer_set_decode_tile", "deinfer_plan_decode_tile",
     "deinfer_plan_raw_tile", "deinfer_plan_decode_stage",
     "deinfer_rank_for_ratio", "deinfer_probe_stream_read", "deinfer_probe_mfma_bf16",
     "deinfer_packed_bytes", "deinfer_pack_factors",
@@ -86,6 +87,8 @@ def lib() -> ctypes.CDLL:
         L.deinfer_set_prefill_token_tile.argtypes = [ctypes.c_int]
         L.deinfer_set_prefill_feature_tile.argtypes = [ctypes.c_int]
         L.deinfer_set_decode_glu_one_launch.argtypes = [ctypes.c_int]
+        L.deinfer_set_decode_tile.argtypes = [ctypes.c_int]
+        L.deinfer_plan_decode_tile.argtypes = [_i64, ctypes.POINTER(_i64), ctypes.c_int, _i64, ctypes.c_int, ctypes.c_int, ctypes.POINTER(ctypes.c_int)]
         L.deinfer_plan_raw_tile.argtypes = [_i64, _i64, _i64, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.POINTER(ctypes.c_int)]
         L.deinfer_plan_decode_stage.argtypes = [_i64, _i64, _i64, ctypes.c_int, ctypes.c_int, ctypes.POINTER(ctypes.c_int)]
         L.deinfer_set_profile_events.argtypes = [ctypes.c_int, _vp, _vp]
@@ -392,6 +395,19 @@ def deinfer_plan_raw_tile(M: int, N: int, K: int, dtype: int, rows4: bool, dual:
     tile = (ctypes.c_int * 3)()
     _check(lib().deinfer_plan_raw_tile(M, N, K, dtype, int(rows4), int(dual), compute_units, tile))
     return tuple(tile)
+
+
+def deinfer_set_decode_tile(form: int) -> None:
+    """Test aid: the second stage of calls of at most 128 tokens as tiles (100 NB + 10 NW + KH), never (-1), or chosen (0)."""
+    _check(lib().deinfer_set_decode_tile(int(form)))
+
+
+def deinfer_plan_decode_tile(T: int, features, k_blocks: int, glu: bool, compute_units: int):
+    """(tokens, features, parts of k) of the tile that such a stage runs as, or None."""
+    tile = (ctypes.c_int * 3)()
+    f = (_i64 * len(features))(*features)
+    _check(lib().deinfer_plan_decode_tile(T, f, len(features), k_blocks, int(glu), compute_units, tile))
+    return tuple(tile) if tile[0] else None
 
 
 def deinfer_plan_decode_stage(T: int, blocks: int, k_blocks: int, glu: bool, compute_units: int) -> int:

@@ -19,7 +19,6 @@
 #include "pack_kernels.h"
 #include "prefill_kernel.h"
 #include "skinny_kernel.h"
-#include "skinny_glu_kernel.h"
 #include "stream_kernel.h"
 #include "probe_kernels.h"
 #include "paged_kernels.h"
@@ -33,6 +32,7 @@ thread_local char g_err[512] = "no error";
 thread_local int g_token_tile = 0;       // 0: chosen per launch; 128 or 256: forced; DEINFER_TOKEN_TILE_BOTH: two shapes in one launch
 thread_local int g_feature_tile = 0;     // 0: chosen per launch; 128 or 256: forced where the token tile is 128
 thread_local int g_glu_width = 0;        // deinfer_set_decode_glu_one_launch: 0 chosen per call; 1 forced; -1 never
+thread_local int g_decode_tile = 0;      // deinfer_set_decode_tile: 0 chosen per call; -1 never; 100 NB + 10 NW + KH forced
 thread_local int g_prof_kernel = 0;      // deinfer_set_profile_events: which internal launch to bracket
 thread_local hipEvent_t g_prof_ev[2] = {nullptr, nullptr};
 
@@ -774,6 +774,12 @@ int deinfer_set_decode_glu_one_launch(int mode) {
   return DEINFER_OK;
 }
 
+int deinfer_set_decode_tile(int form) {
+  if (form < -1) return fail(DEINFER_ERR_INVALID_ARG, "decode tile: 0, -1 or 100 NB + 10 NW + KH, got %d", form);
+  g_decode_tile = form;
+  return DEINFER_OK;
+}
+
 int deinfer_plan_raw_tile(int64_t M, int64_t N, int64_t K, int dtype, int rows4, int dual, int compute_units, int *tile) {
   if (M < 1 || N < 1 || K < 1 || compute_units < 1 || !tile) return fail(DEINFER_ERR_INVALID_ARG, "raw tile: bad argument");
   if (dtype != DEINFER_F32 && dtype != DEINFER_BF16 && dtype != DEINFER_F16) return fail(DEINFER_ERR_UNSUPPORTED, "raw tile: unknown dtype %d", dtype);
@@ -786,6 +792,28 @@ int deinfer_plan_decode_stage(int64_t T, int64_t blocks, int64_t k_blocks, int g
   if (T < 1 || T > SKINNY_MAX_T || blocks < 1 || k_blocks < 1 || compute_units < 1 || !token_blocks) return fail(DEINFER_ERR_INVALID_ARG, "decode stage: bad argument");
   const StChoice c = stream_choice(T, blocks, k_blocks, glu != 0, compute_units);
   *token_blocks = c.on ? c.NB : 0;
+  return DEINFER_OK;
+}
+
+int deinfer_plan_decode_tile(int64_t T, const int64_t *features, int n, int64_t k_blocks, int glu, int compute_units, int *tile) {
+  if (T < 1 || T > SKINNY_MAX_T || !features || n < 1 || n > 3 || k_blocks < 1 || compute_units < 1 || !tile || (glu && n != 1))
+    return fail(DEINFER_ERR_INVALID_ARG, "decode tile: bad argument");
+  deinfer_factors_t f[3];
+  const deinfer_factors_t *pf[3];
+  int64_t otiles[3], blocks = 0;
+  const int np = glu ? 2 : n;
+  memset(f, 0, sizeof(f));
+  for (int i = 0; i < np; ++i) {
+    f[i].d_in = 32; f[i].r = 32 * k_blocks; f[i].d_out = features[glu ? 0 : i];
+    pf[i] = &f[i];
+    if (f[i].d_out < 1) return fail(DEINFER_ERR_INVALID_ARG, "decode tile: bad argument");
+    otiles[i] = ceil_div(f[i].d_out, (int64_t)16);
+    if (!(glu && i == 1)) blocks += ceil_div(otiles[i], (int64_t)2);
+  }
+  const StChoice st = stream_choice(T, blocks, k_blocks, glu != 0, compute_units);
+  const bool wide = glu && !st.on && skinny_glu_one_launch(T, otiles[0], compute_units);
+  SkTile t = tile_choice(T, otiles, n, k_blocks, glu != 0, st, skinny_plan(T, pf, np, glu != 0), wide, compute_units);
+  tile[0] = 32 * t.NB; tile[1] = 32 * t.NW; tile[2] = t.KH;
   return DEINFER_OK;
 }
 

@@ -669,6 +669,66 @@ def test_stages_as_separate_calls(dn, kind, T):
         assert max_err(to_host(h), to_host(h_fused)) <= 2.0 ** -6
 
 
+# ------------------------------------------------------------------ second stages as tiles over the whole k range
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("T", [9, 32, 33, 64, 65, 128])
+def test_second_stage_as_tiles(dn, dtype, T):
+    """Every tile that is built, forced: three products of different ranks and ragged widths in one launch, bias and
+    activation, GLU with ranks of different length, and the staged calls on rank-space rows embedded in NaN (ranks that are
+    no multiple of 8, the last chunk in the first or the second half of the k range)."""
+    import torch
+    d_in = 136
+    x = si.make(61, 1, (T, d_in), 1.0, dtype)
+    bias = si.make(61, 2, (1, 1234), 1.0, dtype)
+    F, host = [], []
+    for i, (r, d_out) in enumerate(((330, 1234), (75, 40), (515, 1234))):
+        U = si.make(61, 10 + 2 * i, (d_in, r), 1.0 / np.sqrt(d_in), dtype)
+        V = si.make(61, 11 + 2 * i, (r, d_out), 1.0 / np.sqrt(r), dtype)
+        F.append(pair(dn, U, V, packed=True)[0])
+        host.append((U.values, V.values))
+    xd, bd = to_dev(x), to_dev(bias).view(-1)
+    ws = dn.Workspace(max(dn.deinfer_workspace_bytes(T, F), dn.deinfer_workspace_bytes(T, [F[0], F[2]])))
+    rows, rows_host = [], []
+    for i, f in enumerate(F):
+        t = si.make(61, 20 + i, (T, f.r), 1.0, dtype)
+        buf = torch.full((T, (f.r + 7) // 8 * 8 + 8), float("nan"), dtype=xd.dtype, device="cuda")
+        buf[:, :f.r] = to_dev(t)
+        rows.append(buf[:, :f.r])
+        rows_host.append(t.values)
+    ref_qkv = oracle.lowrank_qkv(x.values, *host[0], *host[1], *host[2])
+    ref_act = np.maximum(oracle.lowrank_linear(x.values, *host[0]) + bias.values, 0.0)
+    ref_glu = oracle.lowrank_gateup_silu(x.values, *host[0], *host[2])
+    ref_up = [oracle.up_projection(rows_host[i], host[i][1]) for i in (0, 2)]
+    ref_upglu = oracle.up_glu_silu(rows_host[0], host[0][1], rows_host[2], host[2][1])
+
+    def room():
+        return torch.full((T, 1240), 9.0, dtype=xd.dtype, device="cuda")          # pitch > width: nothing may be written past d_out
+    try:
+        for form in (112, 121, 122, 131, 222, 231, 241):
+            dn.deinfer_set_decode_tile(form)
+            out = [room(), room(), room()]
+            dn.deinfer_lowrank_qkv(xd, *F, ws, out=tuple(o[:, :f.d_out] for o, f in zip(out, F)))
+            for o, f, ref in zip(out, F, ref_qkv):
+                assert max_err(to_host(o[:, :f.d_out]), ref) <= TOL[dtype], form
+                assert float((o[:, f.d_out:].float() - 9.0).abs().max()) == 0.0
+            assert max_err(to_host(dn.deinfer_lowrank_linear_act(xd, F[0], ws, bias=bd, act=dn.ACT_RELU)), ref_act) <= TOL[dtype], form
+            for i, ref in zip((0, 2), ref_up):
+                assert max_err(to_host(dn.deinfer_lowrank_up(rows[i], F[i], ws)), ref) <= TOL[dtype], form
+        for form in (111, 121, 141, 221, 241, 441):
+            dn.deinfer_set_decode_tile(form)
+            h = room()
+            dn.deinfer_lowrank_gateup_silu(xd, F[0], F[2], ws, out=h[:, :1234])
+            assert max_err(to_host(h[:, :1234]), ref_glu) <= TOL[dtype], form
+            assert float((h[:, 1234:].float() - 9.0).abs().max()) == 0.0
+            assert max_err(to_host(dn.deinfer_lowrank_up_glu_silu(rows[0], rows[2], F[0], F[2], ws)), ref_upglu) <= TOL[dtype], form
+        ws.check()
+        dn.deinfer_set_decode_tile(999)
+        with pytest.raises(dn.DeinferError):
+            dn.deinfer_lowrank_up(rows[0], F[0], ws)
+    finally:
+        dn.deinfer_set_decode_tile(0)
+
+
 # ------------------------------------------------------------------ the one-launch second stage of the GLU call
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("T", [17, 32, 40, 64, 100, 128])

@@ -118,6 +118,21 @@ def test_every_form_of_a_decode_stage_is_taken_by_the_rows_of_its_test():
     assert forms >= {(g, f, late) for g in (False, True) for f in (0, 1, 2) for late in (False, True)}
 
 
+def test_second_stages_that_run_as_tiles():
+    """Upward projections that were timed in every form (us: other forms / tiles)."""
+    def tile(k, features, T, glu=False):
+        return dn.deinfer_plan_decode_tile(T, features if isinstance(features, list) else [features], -(-k // 32), glu, CUS)
+    assert tile(1640, 8192, 128) == (64, 64, 2)              # 21.5 / 14.4
+    assert tile(1640, [8192, 1024, 1024], 128) == (64, 96, 1)   # 23.1 / 15.7
+    assert tile(512, 10240, 64) in ((32, 96, 1), (64, 128, 1))  # 13.0 / 7.6, 7.8
+    assert tile(1640, 8192, 64) == (32, 64, 2)               # 15.4 / 11.8
+    assert tile(1640, 8192, 128, True) == (64, 64, 1)        # 29.4 / 20.2
+    assert tile(3440, 10240, 64) is None                     # 21.9 / 22.2
+    assert tile(3440, 2048, 32) is None                      # 9.4 / 11.8
+    assert tile(3440, 5504, 64, True) is None                # 22.3 / 27.7
+    assert tile(197, 18336, 128) is None                     # 12.4 / 14.8
+
+
 def test_the_static_scratch_entry_takes_a_split_that_fits():
     """First stages whose best split needs more than the static array, while a smaller one (or none) fits it: not refused for
     lack of scratch (without a device the call then fails for that reason, with one it is not made here)."""
