@@ -154,12 +154,14 @@ def _dtype_code(t) -> int:
 
 
 def _ptr(t) -> Optional[int]:
-    return None if t is None else int(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream(stream) -> Optional[int]:
     import torch
     if stream is None:
+        if torch.cuda.is_initialized():      # the handle of torch.cuda.current_stream(), without making that object (4 us a call)
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()) or None
         stream = torch.cuda.current_stream()
     h = int(stream.cuda_stream)
     return h if h else None
@@ -251,23 +253,25 @@ def deinfer_workspace_bytes(T: int, pairs: Sequence[Pair]) -> int:
 
 def _ld(t) -> int:
     # a single row keeps the pitch of the tensor it was cut from (it decides alignment checks)
-    if t.shape[0] > 1 or int(t.stride(0)) >= int(t.shape[1]):
-        return max(int(t.stride(0)), 1)
-    return max(int(t.shape[1]), 1)
+    shape, pitch = t.shape, t.stride(0)
+    if shape[0] > 1 or pitch >= shape[1]:
+        return max(pitch, 1)
+    return max(shape[1], 1)
 
 
 def _rows(x, what: str):
-    if x.dim() != 2 or (x.shape[1] and x.stride(1) != 1):
+    shape = x.shape
+    if len(shape) != 2 or (shape[1] and x.stride(1) != 1):
         raise ValueError(f"{what} must be a row-major 2-D tensor")
-    return int(x.shape[0])
+    return shape[0]
 
 
 # ------------------------------------------------------------------ the four entry points
 def deinfer_lowrank_linear(x, pair: Pair, ws: Workspace, out=None, stream=None):
     """y = (x U) V."""
-    import torch
     T = _rows(x, "x")
     if out is None:
+        import torch
         out = torch.empty((T, pair.d_out), dtype=x.dtype, device=x.device)
     _check(lib().deinfer_lowrank_linear(_ptr(x), T, _ld(x), ctypes.byref(pair.desc),
                                         _ptr(out), _ld(out), _ptr(ws.buf), ws.nbytes, _stream(stream)))
@@ -283,9 +287,9 @@ def deinfer_lowrank_linear_static(x, pair: Pair, out, stream=None):
 
 def deinfer_lowrank_down(h, pair: Pair, ws: Workspace, out=None, stream=None):
     """y = (h U_d) V_d."""
-    import torch
     T = _rows(h, "h")
     if out is None:
+        import torch
         out = torch.empty((T, pair.d_out), dtype=h.dtype, device=h.device)
     _check(lib().deinfer_lowrank_down(_ptr(h), T, _ld(h), ctypes.byref(pair.desc),
                                       _ptr(out), _ld(out), _ptr(ws.buf), ws.nbytes, _stream(stream)))
@@ -294,10 +298,10 @@ def deinfer_lowrank_down(h, pair: Pair, ws: Workspace, out=None, stream=None):
 
 def deinfer_lowrank_down_proj(x, pairs, ws: Workspace, t_out=None, stream=None):
     """t_i = x U_i for 1 to 3 pairs that share x: the first stage alone.  Returns the list of t_i."""
-    import torch
     T = _rows(x, "x")
     n = len(pairs)
     if t_out is None:       # pitch rounded up to 8 elements: rows that deinfer_lowrank_up reads in place where r % 8 == 0
+        import torch
         t_out = [torch.zeros((T, max((p.r + 7) // 8 * 8, 8)), dtype=x.dtype, device=x.device)[:, :p.r] for p in pairs]
     fa = (ctypes.POINTER(Factors) * n)(*[ctypes.pointer(p.desc) for p in pairs])
     ta = (_vp * n)(*[_ptr(t) for t in t_out])
@@ -308,11 +312,11 @@ def deinfer_lowrank_down_proj(x, pairs, ws: Workspace, t_out=None, stream=None):
 
 def deinfer_lowrank_up_glu_silu(t_gate, t_up, fgate: Pair, fup: Pair, ws: Workspace, out=None, stream=None):
     """h = silu(t_gate V_gate) * (t_up V_up): the second stage of the GLU sub-layer alone."""
-    import torch
     T = _rows(t_gate, "t_gate")
     if _rows(t_up, "t_up") != T:
         raise ValueError("t_gate and t_up must have the same number of rows")
     if out is None:
+        import torch
         out = torch.empty((T, fgate.d_out), dtype=t_gate.dtype, device=t_gate.device)
     _check(lib().deinfer_lowrank_up_glu_silu(_ptr(t_gate), _ld(t_gate), _ptr(t_up), _ld(t_up), T,
                                              ctypes.byref(fgate.desc), ctypes.byref(fup.desc),
@@ -325,9 +329,9 @@ ACT_NONE, ACT_RELU, ACT_GELU = 0, 1, 2
 
 def deinfer_lowrank_linear_act(x, pair: Pair, ws: Workspace, bias=None, act: int = ACT_NONE, out=None, stream=None):
     """y = act((x U) V + bias): first sub-layer of a non-GLU MLP."""
-    import torch
     T = _rows(x, "x")
     if out is None:
+        import torch
         out = torch.empty((T, pair.d_out), dtype=x.dtype, device=x.device)
     _check(lib().deinfer_lowrank_linear_act(_ptr(x), T, _ld(x), ctypes.byref(pair.desc), _ptr(bias), int(act),
                                             _ptr(out), _ld(out), _ptr(ws.buf), ws.nbytes, _stream(stream)))
@@ -371,7 +375,6 @@ def deinfer_kv_compact_copy(pool, block_bytes: int, plan_dev, buffer, stream=Non
 
 def deinfer_rope_inplace(x, n_heads: int, head_dim: int, positions_dev, theta: float = 10000.0, stream=None) -> None:
     """Rotary position embedding in place on x [T, n_heads * head_dim] (pairs i, i + head_dim / 2)."""
-    import torch
     dt = _dtype_code(x)
     _check(lib().deinfer_rope_inplace(_ptr(x), _rows(x, "x"), _ld(x), int(n_heads), int(head_dim), _ptr(positions_dev),
                                       float(theta), dt, _stream(stream)))
@@ -439,9 +442,9 @@ def deinfer_probe_mfma_bf16(operands, n_rounds: int, sink, stream=None) -> float
 
 def deinfer_lowrank_up(t, pair: Pair, ws: Workspace, out=None, stream=None):
     """y = t V: the upward projection alone (rebuilding keys / values from the low-rank cache)."""
-    import torch
     T = _rows(t, "t")
     if out is None:
+        import torch
         out = torch.empty((T, pair.d_out), dtype=t.dtype, device=t.device)
     _check(lib().deinfer_lowrank_up(_ptr(t), T, _ld(t), ctypes.byref(pair.desc),
                                     _ptr(out), _ld(out), _ptr(ws.buf), ws.nbytes, _stream(stream)))
@@ -450,9 +453,9 @@ def deinfer_lowrank_up(t, pair: Pair, ws: Workspace, out=None, stream=None):
 
 def deinfer_rope_table(positions_dev, head_dim: int, theta: float = 10000.0, table=None, stream=None):
     """cos | sin of the rotary angles per token: fp32 [T, head_dim] (cos in the first half of a row)."""
-    import torch
     T = int(positions_dev.numel())
     if table is None:
+        import torch
         table = torch.empty((T, int(head_dim)), dtype=torch.float32, device=positions_dev.device)
     _check(lib().deinfer_rope_table(_ptr(positions_dev), T, int(head_dim), float(theta), _ptr(table), _stream(stream)))
     return table
@@ -474,9 +477,9 @@ def deinfer_lowrank_up_rope(t, pair: Pair, table, ws: Workspace, out=None, strea
 def deinfer_lowrank_qkv(x, fq: Pair, fk: Pair, fv: Pair, ws: Workspace,
                         out=None, t_k=None, t_v=None, stream=None):
     """q, k, v = (x U_q) V_q, (x U_k) V_k, (x U_v) V_v; optional rank-space outputs t_k, t_v."""
-    import torch
     T = _rows(x, "x")
     if out is None:
+        import torch
         out = tuple(torch.empty((T, p.d_out), dtype=x.dtype, device=x.device) for p in (fq, fk, fv))
     q, k, v = out
     _check(lib().deinfer_lowrank_qkv(
@@ -489,9 +492,9 @@ def deinfer_lowrank_qkv(x, fq: Pair, fk: Pair, fv: Pair, ws: Workspace,
 
 def deinfer_lowrank_gateup_silu(x, fgate: Pair, fup: Pair, ws: Workspace, out=None, stream=None):
     """h = silu((x U_g) V_g) * ((x U_u) V_u)."""
-    import torch
     T = _rows(x, "x")
     if out is None:
+        import torch
         out = torch.empty((T, fgate.d_out), dtype=x.dtype, device=x.device)
     _check(lib().deinfer_lowrank_gateup_silu(_ptr(x), T, _ld(x), ctypes.byref(fgate.desc),
                                              ctypes.byref(fup.desc), _ptr(out), _ld(out),
