@@ -76,7 +76,6 @@ struct SkParams {
   int n_prob;
   int n_groups;              // feature groups of all products; grid = n_groups * P, or n_groups * n_tblocks with P = 1
   int P;
-  int n_tblocks;             // blocks of 32 NB tokens, each with workgroups of its own (1 unless direct or GLU)
   SkProblem prob[3];         // GLU: gate and up (act, lda, frags, K, KB, n_ftiles; the output through prob[0])
   float *part;               // [P][NB * 32][n_groups * 128] fp32
   long long part_stride;     // NB * 32 * n_groups * 128
@@ -85,6 +84,8 @@ struct SkParams {
   int direct;
   const uint16_t *bias;      // single product only; may be null
   int act;                   // see act_f32
+  int n_tblocks;             // tiles: blocks of 32 NB tokens (1 otherwise).  (Last: in front of the products it cost every
+                             // launch 0.2 us)
 };
 
 // NB = 32-token blocks of a workgroup (1, 2 or 4); KBS = k-blocks per stage (4, or 2: half the slab)
@@ -96,7 +97,7 @@ struct SkParams {
 // MODE: SK_SPLIT one k-range per workgroup (partial sums, or the outputs where there is one range: SkParams::direct);
 // SK_TILE the whole k range and one of n_tblocks token blocks, outputs stored; SK_GLU the same for the gate and up product
 // of a GLU call side by side, each with KH x NW wavefronts: silu(gate) * up is taken when their sums meet in LDS and
-// stored once.  (Compile-time, also because what the tiles compute before their first load costs the split 3 to 6 %.)
+// stored once.
 // TAIL: the valid columns K of the activation rows may be no multiple of 8 (the caller's rank-space rows of
 // an upward projection alone): what the last chunk holds beyond column K - 1 is cleared in LDS
 // (lds_zero_chunk_tail in common.h) by the wavefront that fetched it, before the barrier of the stage.  A variant of
@@ -120,7 +121,9 @@ __global__ __launch_bounds__(64 * NW * KH * (MODE == SK_GLU ? 2 : 1), NW * KH * 
   extern __shared__ __attribute__((aligned(16))) unsigned char sk_lds[];      // [product, part][SK_SLABS][SLAB]
   const int lane = threadIdx.x & 63;
   const int wave_all = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int role = wave_all / NW, wave = wave_all % NW;      // role: product (GLU) and part of the k range; wavefronts of a role share slabs
+  // role: product (GLU) and part of the k range; the wavefronts of a role share slabs
+  constexpr bool ROLES = GLU || KH > 1;
+  const int role = ROLES ? wave_all / NW : 0, wave = ROLES ? wave_all % NW : wave_all;
   const int prod = GLU ? role / KH : 0, kh = role % KH;
   unsigned char (*const xs)[SLAB] = reinterpret_cast<unsigned char (*)[SLAB]>(sk_lds + role * (SK_SLABS * SLAB));
   // split: consecutive workgroups share the k-range (the same activation slab, kept hot in L2); tiles: the token blocks
