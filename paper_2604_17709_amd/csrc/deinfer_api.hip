@@ -157,13 +157,18 @@ SkPlan skinny_plan(int64_t T, const deinfer_factors_t *const *f, int n, bool glu
   for (int s = 0; s < 2; ++s) {
     // more than 8 ranges only for a very long k (first stage of the second MLP layer of the largest
     // models): every range keeps at least 64 k-blocks (70B shapes, k = 28672, 20 groups: 12 ranges,
-    // 70 -> 65 us at T = 128; the 7B shapes, k = 11008, were slower with more than 8)
+    // 70 -> 65 us at T = 128; the 7B shapes, k = 11008, were slower with more than 8).  Few feature groups leave the
+    // device empty, and their partial sums are small: up to three groups keep 16 k-blocks per range, up to six 16 above 64
+    // tokens and 32 below (first stage alone, us: 8192 x 297 at 128 tokens 15.0 -> 13.7, 11008 x 299 18.6 -> 15.7,
+    // 14336 x 640 21.2 -> 17.4, at 32 tokens 14.8 -> 13.4; 8192 x 638 at 32 tokens would be 11.5 -> 12.0 with 16, ten
+    // groups, 8192 x 1200, at 32 tokens 12.1 -> 12.5)
     int cap = 8;
+    const int g4 = groups_of(s, 4);
     if (s == 0) {
-      const int by_k = (int)(ceil_div(f[0]->d_in, 32) / 64);
+      const int keep = g4 <= 3 || (g4 <= 6 && T > 64) ? 16 : g4 <= 6 ? 32 : 64;
+      const int by_k = (int)(ceil_div(f[0]->d_in, 32) / keep);
       cap = by_k > SK_MAX_PARTS ? SK_MAX_PARTS : by_k > 8 ? by_k : 8;
     }
-    const int g4 = groups_of(s, 4);
     const bool direct = s == 1 && !glu && (g4 > target / 2 || g4 >= SK_DIRECT_MIN_GROUPS);
     if (direct) cap = 1;
     auto ranges = [&](int g) { const int p = target / (g > 0 ? g : 1); return p < 1 ? 1 : p > cap ? cap : p; };

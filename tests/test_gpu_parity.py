@@ -729,6 +729,22 @@ def test_second_stage_as_tiles(dn, dtype, T):
         dn.deinfer_set_decode_tile(0)
 
 
+@pytest.mark.parametrize("T,ranks", [(17, (40,)), (64, (130, 46, 46)), (128, (297,)), (128, (400, 260)), (100, (700,))])
+def test_first_stages_of_few_feature_groups(dn, T, ranks):
+    """Long k and few features: more than eight k-ranges of 16 or 32 k-blocks (the last one shorter), summed in two rounds
+    of the adding launch."""
+    d_in = 8192 + 40
+    x = si.make(71, 1, (T, d_in), 1.0, "bf16")
+    F, U = [], []
+    for i, r in enumerate(ranks):
+        U.append(si.make(71, 10 + 2 * i, (d_in, r), 1.0 / np.sqrt(d_in), "bf16"))
+        F.append(pair(dn, U[-1], si.make(71, 11 + 2 * i, (r, 16), 1.0, "bf16"), packed=True)[0])
+    ws = ws_for(dn, T, F)
+    for t, u in zip(dn.deinfer_lowrank_down_proj(to_dev(x), F, ws), U):
+        assert max_err(to_host(t), oracle.up_projection(x.values, u.values)) <= TOL["bf16"]
+    ws.check()
+
+
 # ------------------------------------------------------------------ the one-launch second stage of the GLU call
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("T", [17, 32, 40, 64, 100, 128])
