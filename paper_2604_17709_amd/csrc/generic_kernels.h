@@ -11,8 +11,10 @@ namespace deinfer {
 // twice the vector rate; every operand is converted to fp32 exactly, so nothing is rounded before the sum).
 // A wavefront owns (16 MB) rows x (16 NV) columns and reads both operands from memory straight into the
 // registers the product wants, no LDS and no barrier in the loop:
-//   * a step is 16 k: lane l works for the k-group g = l / 16 on k = 4 g .. 4 g + 3, so the A operand of four
-//     products is one load of 4 consecutive elements of row l % 16;
+//   * a step is 16 k: lane l works for the k-group g = l / 16 on k = 4 g .. 4 g + 3 of A row l % 16.  Loaded that way, 16
+//     neighbouring lanes touch 16 rows and the address unit, which the wavefronts share, takes four times as long as for
+//     whole pieces: four neighbouring lanes load the 16 k of one row instead, and a lane permutation (ds_bpermute)
+//     brings each value to its lane, one step ahead of the products;
 //   * B rows are read NV elements per lane: lane l holds columns NV (l % 16) .. + NV - 1 of row 4 g + e, and
 //     product j takes element j, i.e. column block j is the columns NV c + j.  A load instruction covers
 //     16 NV consecutive columns of four rows, and a lane ends up with NV consecutive output columns.
@@ -20,6 +22,10 @@ namespace deinfer {
 // order (deterministic).  A 64 x 64 tile reads 16 bytes per clock and compute unit at the full matrix rate,
 // half of what a compute unit takes in from L2.  What bounds it: the fp32 matrix rate (157 TFLOP/s) for
 // many rows, the stream of B and the latency of the first loads for few.
+// Measured (first stage alone / both, us): 201 x 4096 x 1638 in fp32 53.4 -> 49.3 / 84.9 -> 81.1 with the permutation,
+// 47.5 / 79.2 with runs of tiles per XCD (below); 100 x 4096 x 2000 37.7 -> 34.3 -> 29.8; 64 x 4096 x 1638 33.3 -> 33.2 ->
+// 26.1; 2048 x 512 x 200 14.5 -> 13.1.  Eight wavefronts on a tile (61.3) and 32 k per step, so that A's lines are
+// loaded whole (54.0), were no faster than 53.4.
 template <typename T> struct RawStore { typedef uint16_t type; };
 template <> struct RawStore<float> { typedef float type; };
 // (loads of several elements need no more than element alignment)
@@ -41,7 +47,7 @@ template <typename TA, typename TB> struct RawOperands {
 
 // register buffers of k-steps in flight: about 16 KiB per wavefront for the large tiles (the loads of a step
 // are requested 2 x 2000 matrix cycles ahead), more steps where a step is small
-constexpr int raw_depth(int mb, int nv) { return mb * nv >= 16 ? 3 : mb * nv >= 8 ? 4 : 6; }
+constexpr int raw_depth(int mb, int nv) { return mb * nv >= 16 ? 4 : mb * nv >= 8 ? 5 : 7; }
 
 // acc[i][j] += A[m0 + 16 i .., :] . B[:, column block j of n0 ..], this wavefront's part of the k range.
 // EDGE: the tile reaches beyond column N - 1 (columns clamped; what they give is not stored).
@@ -57,12 +63,16 @@ __device__ __forceinline__ void raw_product(const RawOperands<TA, TB> &P, int M,
   const int c = lane & 15, g = lane >> 4;
   const int steps = (P.K + 15) / 16, full = P.K / 16;
   const int s_begin = (int)((int64_t)steps * wave / NW), s_end = (int)((int64_t)steps * (wave + 1) / NW);
+  // A is loaded with four neighbouring lanes on 4 x 4 consecutive k of one row, and crosses to the lanes that multiply
+  // it (row l % 16, k-group l / 16) by a lane permutation
+  const int ak = 4 * (lane & 3);
+  const int from = (4 * c + g) * 4;
   const AS *a[MB];
 #pragma unroll
   for (int i = 0; i < MB; ++i) {
-    int64_t row = m0 + 16 * i + c;
+    int64_t row = m0 + 16 * i + (lane >> 2);
     row = row < M ? row : M - 1;                       // (rows beyond M - 1 are not stored)
-    a[i] = reinterpret_cast<const AS *>(P.A) + row * P.lda + 4 * g;
+    a[i] = reinterpret_cast<const AS *>(P.A) + row * P.lda + ak;
   }
   int64_t col[EDGE ? NV : 1];
 #pragma unroll
@@ -83,12 +93,21 @@ __device__ __forceinline__ void raw_product(const RawOperands<TA, TB> &P, int M,
     }
     if (e < MB) t.a[e] = *reinterpret_cast<const AV *>(a[e] + (int64_t)16 * s);
   };
-  auto multiply = [&](const Step &t, int e) {
+  struct Rows { AV a[MB]; };
+  auto cross = [&](const AV &v) -> AV {
+    constexpr int W = (int)sizeof(AV) / 4;
+    typedef int words __attribute__((ext_vector_type(W)));
+    words w = __builtin_bit_cast(words, v);
+#pragma unroll
+    for (int q = 0; q < W; ++q) w[q] = __builtin_amdgcn_ds_bpermute(from, w[q]);
+    return __builtin_bit_cast(AV, w);
+  };
+  auto multiply = [&](const Rows &r, const Step &t, int e) {
 #pragma unroll
     for (int j = 0; j < NV; ++j)
 #pragma unroll
       for (int i = 0; i < MB; ++i)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(raw_cvt<TA>(t.a[i][e]), raw_cvt<TB>(t.b[e][j]), acc[i][j], 0, 0, 0);
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(raw_cvt<TA>(r.a[i][e]), raw_cvt<TB>(t.b[e][j]), acc[i][j], 0, 0, 0);
   };
   const bool tail = s_end == steps && full < steps;
   const int s_stop = s_end < full ? s_end : full;
@@ -98,10 +117,11 @@ __device__ __forceinline__ void raw_product(const RawOperands<TA, TB> &P, int M,
   if (tail) {
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      int k = 16 * full + 4 * g + e;
+      int k = 16 * full + 4 * g + e, ka = 16 * full + ak + e;
       k = k < P.K ? k : P.K - 1;
+      ka = ka < P.K ? ka : P.K - 1;
 #pragma unroll
-      for (int i = 0; i < MB; ++i) rest.a[i][e] = a[i][k - 4 * g];
+      for (int i = 0; i < MB; ++i) rest.a[i][e] = a[i][ka - ak];
 #pragma unroll
       for (int j = 0; j < NV; ++j) rest.b[e][j] = b[(int64_t)(k - 4 * g) * P.ldb + (EDGE ? col[EDGE ? j : 0] : col[0] + j)];
     }
@@ -116,36 +136,51 @@ __device__ __forceinline__ void raw_product(const RawOperands<TA, TB> &P, int M,
       }
   }
   if (tail) {
+    Rows r;
+#pragma unroll
+    for (int i = 0; i < MB; ++i) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) rest.a[i][e] = 16 * full + ak + e < P.K ? rest.a[i][e] : AS{};
+      r.a[i] = cross(rest.a[i]);
+    }
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const bool in = 16 * full + 4 * g + e < P.K;
 #pragma unroll
-      for (int i = 0; i < MB; ++i) rest.a[i][e] = in ? rest.a[i][e] : AS{};
-#pragma unroll
       for (int j = 0; j < NV; ++j) rest.b[e][j] = in ? rest.b[e][j] : BS{};
-      multiply(rest, e);
+      multiply(r, rest, e);
     }
   }
   if (s_begin < s_stop) {
     int s = s_begin;
-    // Step s is multiplied while step s + D - 1 is requested, a quarter behind each quarter of the products.
+    // Step s is multiplied while step s + D - 1 is requested and the rows of step s + 1 cross, a quarter behind each
+    // quarter of the products.
     // (No exit inside a round of D steps: with one, the compiler waits for every outstanding load at the top.)
+    Rows r;
+#pragma unroll
+    for (int i = 0; i < MB; ++i) r.a[i] = cross(buf[0].a[i]);
     for (; s + D <= s_stop; s += D) {
 #pragma unroll
-      for (int d = 0; d < D; ++d)
+      for (int d = 0; d < D; ++d) {
+        Rows next;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          multiply(buf[d], e);
+          multiply(r, buf[d], e);
           __builtin_amdgcn_sched_barrier(0);
           load(buf[(d + D - 1) % D], s + d + D - 1 < last ? s + d + D - 1 : last, e);
+          if (e < MB) next.a[e] = cross(buf[(d + 1) % D].a[e]);
           __builtin_amdgcn_sched_barrier(0);
         }
+        r = next;
+      }
     }
 #pragma unroll
     for (int d = 0; d < D - 1; ++d)
       if (s + d < s_stop) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) multiply(buf[d], e);
+        for (int i = 0; i < MB; ++i) r.a[i] = cross(buf[d].a[i]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) multiply(r, buf[d], e);
       }
   }
 #else
@@ -153,6 +188,7 @@ __device__ __forceinline__ void raw_product(const RawOperands<TA, TB> &P, int M,
 #endif
 }
 
+constexpr unsigned RAW_RUN_ROWS = 8;
 // C = act(A.B + bias), or (DUAL) C = silu(A.B) * (A2.B2).  One workgroup of NW wavefronts = one tile of
 // 16 MB rows x 16 NV columns; the tiles of a column block are consecutive workgroups (they share B's columns).
 // bias: one value per column of C (may be null), act: see act_f32.
@@ -165,7 +201,16 @@ __global__ __launch_bounds__(64 * NW) void raw_gemm_kernel(
   typedef float sum_t __attribute__((ext_vector_type(NV)));
   __shared__ sum_t part[NW][UNITS][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t m0 = (int64_t)blockIdx.x * (16 * MB), n0 = ((int64_t)blockIdx.z * gridDim.y + blockIdx.y) * (16 * NV);
+  // Few row tiles: an XCD takes a run of tiles, so that the row tiles of a column block share one L2, which fetches B's
+  // columns once
+  int mt = blockIdx.x;
+  int64_t nt = (int64_t)blockIdx.z * gridDim.y + blockIdx.y;
+  if (gridDim.x > 1 && gridDim.x <= RAW_RUN_ROWS && gridDim.z == 1) {
+    const int tile = run_tile_of((int)(blockIdx.y * gridDim.x + blockIdx.x), (int)(gridDim.y * gridDim.x));
+    nt = tile / (int)gridDim.x;
+    mt = tile - (int)nt * (int)gridDim.x;
+  }
+  const int64_t m0 = (int64_t)mt * (16 * MB), n0 = nt * (16 * NV);
   if (n0 >= N) return;                                 // (the last slice of the column blocks)
   const bool edge = n0 + 16 * NV > N;
   float sum[DUAL ? 2 : 1][UPW][NV];
