@@ -185,6 +185,9 @@ __global__ __launch_bounds__(64 * NW * KH * (MODE == SK_GLU ? 2 : 1), NW * KH * 
   }
   const unsigned xkend = (unsigned)(((Q.K + 7) >> 3) * 16);      // bytes of a row up to the end of the chunk that holds column K - 1
   const unsigned xklim = (unsigned)(Q.K * 2 - 16);               // (K a multiple of 8: the last chunk)
+  // tiles: chunks beyond K or this wavefront's k range read zeros (the parts and stages are rounded up by more k-blocks than
+  // those of the forms that they replace, and an infinite activation that met their zero weights would give NaN)
+  const unsigned xend = xkend < (unsigned)kb_end * 64u ? xkend : (unsigned)kb_end * 64u;
   // the chunk with columns that are not to be used: its stage (of this wavefront's k-range) and its slot there
   const int krem = Q.K & 7;
   const int kb_fix = Q.K >> 5;
@@ -200,13 +203,17 @@ __global__ __launch_bounds__(64 * NW * KH * (MODE == SK_GLU ? 2 : 1), NW * KH * 
       wn[idx] = __builtin_amdgcn_raw_buffer_load_b128(wres, off.lane + (idx & 1) * 512, off.scalar, 2);
     } else {
       const int i = idx - KBS * 2;
-      // uniform; OR-ed in: no branch around the loads.  (GLU: the shorter product has no slabs past its own range)
-      const unsigned dead = (GLU ? kb_begin + fst * KBS < kb_end : fst < n_stages) ? 0u : OOB;
-      // chunks beyond K re-read a chunk of valid columns (the last one; TAIL: the first one), which meets zero weights
       unsigned kb = (unsigned)(kb_begin + fst * KBS) * 64u + xchunk[i];
-      kb = TAIL ? (kb < xkend ? kb : 0u) : (kb < xklim ? kb : xklim);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(xres, (DEINFER_LDS_PTR void *)&xs[fbuf][xm[i] * RPI * XROW], 16,
-                                               (xrow[i] + kb) | dead, 0, 0, 0);
+      unsigned off;
+      if constexpr (MODE == SK_SPLIT) {
+        const unsigned dead = fst < n_stages ? 0u : OOB;      // uniform; OR-ed in: no branch around the loads
+        // chunks beyond K re-read a chunk of valid columns (the last one; TAIL: the first one), which meets zero weights
+        kb = TAIL ? (kb < xkend ? kb : 0u) : (kb < xklim ? kb : xklim);
+        off = (xrow[i] + kb) | dead;
+      } else {
+        off = kb < xend ? xrow[i] + kb : OOB;
+      }
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(xres, (DEINFER_LDS_PTR void *)&xs[fbuf][xm[i] * RPI * XROW], 16, off, 0, 0, 0);
     }
   };
 

@@ -729,6 +729,39 @@ def test_second_stage_as_tiles(dn, dtype, T):
         dn.deinfer_set_decode_tile(0)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("r", [96, 819, 832, 872])
+def test_infinite_rank_space_values_in_tiles(dn, dtype, r):
+    """k ranges that end inside a stage, or leave the second half of the range partly or wholly empty: one infinite value
+    in a row and positive weights give infinite outputs in that row (no product with what lies past the range), and the
+    other rows stay as they are."""
+    import torch
+    T, d_out = 70, 328
+    td = torch.float16 if dtype == "f16" else torch.bfloat16
+    U = si.make(63, 1, (8, r), 1.0, dtype)
+    V = [abs(to_dev(si.make(63, 2 + i, (r, d_out), 1.0 / r, dtype)).float()).clamp_min_(1e-4).to(td) for i in range(2)]
+    F = [dn.deinfer_pack_factors(dn.raw_pair(to_dev(U), v)) for v in V]
+    ws = ws_for(dn, T, F)
+    rows = torch.full((T, (r + 7) // 8 * 8 + 8), float("nan"), dtype=td, device="cuda")
+    rows[:, :r] = abs(to_dev(si.make(63, 9, (T, r), 1.0, dtype)).float()).to(td)
+    t = rows[:, :r]
+    bad = {3: 0, 33: r - 1, 34: r - 9, 69: r // 2}
+    for row, col in bad.items():
+        t[row, col] = float("inf")
+    good = [i for i in range(T) if i not in bad]
+    ref = oracle.up_projection(to_host(t)[good], to_host(V[0]))
+    ref_glu = oracle.up_glu_silu(to_host(t)[good], to_host(V[0]), to_host(t)[good], to_host(V[1]))
+    try:
+        for glu, forms in ((False, (112, 121, 122, 131, 222, 231, 241)), (True, (111, 121, 141, 221, 241, 441))):
+            for form in forms:
+                dn.deinfer_set_decode_tile(form)
+                y = dn.deinfer_lowrank_up_glu_silu(t, t, F[0], F[1], ws) if glu else dn.deinfer_lowrank_up(t, F[0], ws)
+                assert bool((y[list(bad)] == float("inf")).all()), (glu, form)
+                assert max_err(to_host(y)[good], ref_glu if glu else ref) <= TOL[dtype], (glu, form)
+    finally:
+        dn.deinfer_set_decode_tile(0)
+
+
 @pytest.mark.parametrize("T,ranks", [(17, (40,)), (64, (130, 46, 46)), (128, (297,)), (128, (400, 260)), (100, (700,))])
 def test_first_stages_of_few_feature_groups(dn, T, ranks):
     """Long k and few features: more than eight k-ranges of 16 or 32 k-blocks (the last one shorter), summed in two rounds
