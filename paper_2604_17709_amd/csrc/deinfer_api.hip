@@ -627,6 +627,8 @@ int run_group(Group gq) {
       const int64_t ld = i == 1 ? gq.ldx2 : gq.ldx;
       const int64_t r = gq.f[i]->r;
       if (!aligned(xi, 16) || ld % 8 != 0 || (r % 8 != 0 && r < 8)) repack = true;
+      // (the kernels address rows with 32-bit byte offsets: the schedules refuse such a first set and cannot see the second)
+      if (i == 1 && gq.T * ld * 2 >= (1ll << 31)) repack = true;
     }
     if (repack) {
       int64_t pitch = 0, col[3] = {0, 0, 0};

@@ -729,6 +729,22 @@ def test_second_stage_as_tiles(dn, dtype, T):
         dn.deinfer_set_decode_tile(0)
 
 
+@pytest.mark.parametrize("T,pitch", [(3, 1 << 30), (140, 1 << 24)])
+def test_second_set_of_rank_space_rows_with_a_very_large_pitch(dn, T, pitch):
+    """Rows of the up pair 2^25 and 2^31 bytes apart (the last one beyond 2^32 bytes): the rows that the caller means."""
+    import torch
+    r, d_out = 40, 264
+    U = si.make(64, 1, (8, r), 1.0, "bf16")
+    V = [si.make(64, 2 + i, (r, d_out), 1.0 / np.sqrt(r), "bf16") for i in range(2)]
+    F = [pair(dn, U, v, packed=True)[0] for v in V]
+    rows = [si.make(64, 4 + i, (T, r), 1.0, "bf16") for i in range(2)]
+    far = torch.empty((T - 1) * pitch + r, dtype=torch.bfloat16, device="cuda").as_strided((T, r), (pitch, 1))
+    far.copy_(to_dev(rows[1]))
+    ws = ws_for(dn, T, F)
+    h = dn.deinfer_lowrank_up_glu_silu(to_dev(rows[0]), far, F[0], F[1], ws)
+    assert max_err(to_host(h), oracle.up_glu_silu(rows[0].values, V[0].values, rows[1].values, V[1].values)) <= TOL["bf16"]
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("r", [96, 819, 832, 872])
 def test_infinite_rank_space_values_in_tiles(dn, dtype, r):
