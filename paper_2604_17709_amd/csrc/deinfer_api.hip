@@ -131,7 +131,8 @@ constexpr int SK_DIRECT_MIN_GROUPS = 96;
 // wider split (105, 115 and 130 were timed: the lowest was best or equal on every block).
 constexpr int SK_NARROW_GAIN_PCT = 105;
 
-SkPlan skinny_plan(int64_t T, const deinfer_factors_t *const *f, int n, bool glu) {
+// more: first stages of few feature groups take more than eight k-ranges
+SkPlan skinny_plan_of(int64_t T, const deinfer_factors_t *const *f, int n, bool glu, bool more) {
   SkPlan pl;
   pl.NB = T <= 32 ? 1 : T <= 64 ? 2 : 4;
   pl.rtot_pad = 0;
@@ -165,7 +166,7 @@ SkPlan skinny_plan(int64_t T, const deinfer_factors_t *const *f, int n, bool glu
     int cap = 8;
     const int g4 = groups_of(s, 4);
     if (s == 0) {
-      const int keep = g4 <= 3 || (g4 <= 6 && T > 64) ? 16 : g4 <= 6 ? 32 : 64;
+      const int keep = !more ? 64 : g4 <= 3 || (g4 <= 6 && T > 64) ? 16 : g4 <= 6 ? 32 : 64;
       const int by_k = (int)(ceil_div(f[0]->d_in, 32) / keep);
       cap = by_k > SK_MAX_PARTS ? SK_MAX_PARTS : by_k > 8 ? by_k : 8;
     }
@@ -188,6 +189,12 @@ SkPlan skinny_plan(int64_t T, const deinfer_factors_t *const *f, int n, bool glu
   const size_t p1 = (size_t)pl.P[1] * pl.NB * 32 * (size_t)pl.groups[1] * (32 * pl.NW[1]) * 4;
   pl.part_bytes = (size_t)round_up((int64_t)(p0 > p1 ? p0 : p1), 256);
   return pl;
+}
+// limit: the bytes of the caller's workspace.  One that holds the partial sums of eight ranges, not those of more, is enough
+// (a workspace sized for other calls, or fixed in a program, was before few groups took more)
+SkPlan skinny_plan(int64_t T, const deinfer_factors_t *const *f, int n, bool glu, size_t limit) {
+  const SkPlan pl = skinny_plan_of(T, f, n, glu, true);
+  return WS_HEADER + pl.t_bytes + pl.part_bytes > limit ? skinny_plan_of(T, f, n, glu, false) : pl;
 }
 
 // ---- k-split of the first stage of a compute-bound call
@@ -294,7 +301,7 @@ size_t workspace_need_of(int64_t T, const deinfer_factors_t *const *pairs, int n
     scratch = round_up((int64_t)tdec, 256) + round_up((int64_t)tpre, 256);
     if (T <= SKINNY_MAX_T) { // (the upward-projection-only call uses this schedule for every such T)
       for (int glu = 0; glu < 2; ++glu) {      // (the call is not known here: room for either kind)
-        const SkPlan pl = skinny_plan(T, pairs, n, glu != 0);
+        const SkPlan pl = skinny_plan(T, pairs, n, glu != 0, limit);
         const size_t sk = pl.t_bytes + pl.part_bytes;
         if (sk > scratch) scratch = sk;
       }
@@ -610,7 +617,7 @@ int run_group(Group gq) {
     }
   if (!gq.ws) return fail(DEINFER_ERR_WORKSPACE, "workspace pointer is NULL");
   if (!aligned(gq.ws, 256)) return fail(DEINFER_ERR_MISALIGNED, "workspace must be 256-byte aligned");
-  const size_t need = workspace_need(gq.T, gq.f, gq.n, gq.fixed_scratch ? gq.ws_bytes : NO_LIMIT);
+  const size_t need = workspace_need(gq.T, gq.f, gq.n, gq.fixed_scratch || gq.T <= SKINNY_MAX_T ? gq.ws_bytes : NO_LIMIT);
   if (gq.ws_bytes < need)
     return fail(DEINFER_ERR_WORKSPACE, "workspace too small: %zu bytes given, %zu needed", gq.ws_bytes, need);
   const bool packed = gq.f[0]->layout == DEINFER_LAYOUT_PACKED;
@@ -819,7 +826,7 @@ int deinfer_plan_decode_tile(int64_t T, const int64_t *features, int n, int64_t 
   }
   const StChoice st = stream_choice(T, blocks, k_blocks, glu != 0, compute_units);
   const bool wide = glu && !st.on && skinny_glu_one_launch(T, otiles[0], compute_units);
-  SkTile t = tile_choice(T, otiles, n, k_blocks, glu != 0, st, skinny_plan(T, pf, np, glu != 0), wide, compute_units);
+  SkTile t = tile_choice(T, otiles, n, k_blocks, glu != 0, st, skinny_plan(T, pf, np, glu != 0, NO_LIMIT), wide, compute_units);
   tile[0] = 32 * t.NB; tile[1] = 32 * t.NW; tile[2] = t.KH;
   return DEINFER_OK;
 }

@@ -25,6 +25,14 @@ RAW_ROWS = [
 ]
 
 
+def workspace_of_eight_ranges(dn, T, pair) -> int:
+    """Bytes that a packed pair's first stage with a long k and few features runs in as eight k-ranges instead of sixteen."""
+    t = -(-(32 if T <= 32 else 64 if T <= 64 else 128) * -(-pair.desc.r // 32) * 32 * 2 // 256) * 256
+    part = dn.deinfer_workspace_bytes(T, [pair]) - 256 - t
+    assert part % 16 == 0
+    return 256 + t + part // 2
+
+
 def to_dev(t: si.Tensor):
     import torch
     if t.dtype == "f32":

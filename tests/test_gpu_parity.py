@@ -7,7 +7,7 @@ import pytest
 import oracle
 import synth_inputs as si
 from oracle import paged_cache as pc
-from gpu_util import RAW_ROWS, TOKEN_TILE_BOTH, TOL, max_err, pair, to_dev, to_host
+from gpu_util import RAW_ROWS, TOKEN_TILE_BOTH, TOL, max_err, pair, to_dev, to_host, workspace_of_eight_ranges
 
 pytestmark = pytest.mark.gpu
 
@@ -792,6 +792,19 @@ def test_first_stages_of_few_feature_groups(dn, T, ranks):
     for t, u in zip(dn.deinfer_lowrank_down_proj(to_dev(x), F, ws), U):
         assert max_err(to_host(t), oracle.up_projection(x.values, u.values)) <= TOL["bf16"]
     ws.check()
+
+
+@pytest.mark.parametrize("T", [32, 64, 128])
+def test_first_stage_of_few_feature_groups_in_a_smaller_workspace(dn, T):
+    import torch
+    x, U, V = gen(72, T, 8192, 297, 64, "bf16")
+    p, keep = pair(dn, U, V, packed=True)
+    ref = oracle.lowrank_linear(x.values, U.values, V.values)
+    n = workspace_of_eight_ranges(dn, T, p)
+    buf = torch.full((2 * n,), 7, dtype=torch.uint8, device="cuda")      # (nothing is written past the workspace)
+    y = dn.deinfer_lowrank_linear(to_dev(x), p, dn.Workspace(n, buf=buf[:n]))
+    assert max_err(to_host(y), ref) <= TOL["bf16"]
+    assert bool((buf[n:] == 7).all())
 
 
 # ------------------------------------------------------------------ the one-launch second stage of the GLU call

@@ -8,7 +8,7 @@ import pytest
 import torch
 
 import paper_2604_17709_amd as dn
-from gpu_util import RAW_ROWS
+from gpu_util import RAW_ROWS, workspace_of_eight_ranges
 
 CUS = 256
 DTYPES = {"f32": dn.F32, "bf16": dn.BF16, "f16": dn.F16}
@@ -144,3 +144,17 @@ def test_the_static_scratch_entry_takes_a_split_that_fits():
         assert dn.deinfer_workspace_bytes(T, [types.SimpleNamespace(desc=f)]) > dn.STATIC_SCRATCH_BYTES
         rc = dn.lib().deinfer_lowrank_linear_static(1 << 30, T, d_in, ctypes.byref(f), 1 << 31, 64, None)
         assert rc == dn.ERR_DEVICE, dn.last_error()
+
+
+@pytest.mark.parametrize("T", [32, 64, 128])
+def test_a_workspace_of_eight_ranges_is_taken(T):
+    """Few feature groups and a long k: more than eight k-ranges where the workspace holds their sums, eight in a smaller one
+    (without a device the call then fails for that reason; one byte less is refused)."""
+    if torch.cuda.is_available():
+        pytest.skip("the pointers are not real")
+    f = dn.Factors()
+    f.U, f.V, f.d_in, f.d_out, f.r, f.dtype, f.layout = 1 << 28, 1 << 29, 8192, 64, 297, dn.BF16, dn.LAYOUT_PACKED
+    n = workspace_of_eight_ranges(dn, T, types.SimpleNamespace(desc=f))
+    call = lambda ws: dn.lib().deinfer_lowrank_linear(1 << 30, T, 8192, ctypes.byref(f), 1 << 31, 64, 1 << 32, ws, None)
+    assert call(n) == dn.ERR_DEVICE, dn.last_error()
+    assert call(n - 1) == dn.ERR_WORKSPACE
