@@ -62,9 +62,10 @@ int deinfer_set_decode_glu_one_launch(int mode);
 
 /*
  * The second stage of a call of at most 128 tokens on packed pairs, for the calls of THIS THREAD (those that do not take
- * the kernels of 8 tokens and fewer): 0 (the default) lets every call choose; -1 never as tiles over the whole k range;
- * 100 NB + 10 NW + KH forces tiles of 32 NB tokens x 32 NW features with KH parts of the k range side by side in a
- * workgroup (a form that is not built makes the call return DEINFER_ERR_UNSUPPORTED).
+ * the kernels of 8 tokens and fewer): 0 (the default) lets every call choose; -1 never as tiles over the whole k range
+ * (unless deinfer_set_decode_glu_one_launch asks for them); 100 NB + 10 NW + KH forces tiles of 32 NB tokens x 32 NW
+ * features with KH parts of the k range side by side in a workgroup.  With a form that is not built for its kind of second
+ * stage a call returns DEINFER_ERR_UNSUPPORTED and enqueues nothing.
  */
 int deinfer_set_decode_tile(int form);
 
@@ -84,9 +85,10 @@ int deinfer_plan_raw_tile(int64_t M, int64_t N, int64_t K, int dtype, int rows4,
 int deinfer_plan_decode_stage(int64_t T, int64_t blocks, int64_t k_blocks, int glu, int compute_units, int *token_blocks);
 
 /*
- * Whether the second stage of such a call runs as tiles over the whole k range instead (host only): tile[0] x tile[1] =
- * tokens x features of a workgroup, tile[2] = parts of the k range inside it; tile[0] = 0: the other forms.  features: of
- * the n products of the call (glu: n = 1, of one of the two), k_blocks: the longest k range.
+ * Whether the second stage of such a call runs as tiles over the whole k range instead, on a device of `compute_units`
+ * units (host only): tile[0] x tile[1] = tokens x features of a workgroup, tile[2] = parts of the k range inside it;
+ * tile[0] = 0: the other forms.  features: of the n products of the call (glu: n = 1, of one of the two), k_blocks: the
+ * longest k range.
  */
 int deinfer_plan_decode_tile(int64_t T, const int64_t *features, int n, int64_t k_blocks, int glu, int compute_units, int *tile);
 

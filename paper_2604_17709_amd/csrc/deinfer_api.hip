@@ -10,6 +10,7 @@
 #include <cstdio>
 #include <cstring>
 #include <atomic>
+#include <initializer_list>
 #include <mutex>
 #include <type_traits>
 
@@ -132,7 +133,9 @@ constexpr int SK_DIRECT_MIN_GROUPS = 96;
 constexpr int SK_NARROW_GAIN_PCT = 105;
 
 // more: first stages of few feature groups take more than eight k-ranges
-SkPlan skinny_plan_of(int64_t T, const deinfer_factors_t *const *f, int n, bool glu, bool more) {
+// cus: the compute units; 256, the count of the device this is written for, where no device can be asked (the host-only size
+// query on a machine without a GPU)
+SkPlan skinny_plan_of(int64_t T, const deinfer_factors_t *const *f, int n, bool glu, bool more, int cus) {
   SkPlan pl;
   pl.NB = T <= 32 ? 1 : T <= 64 ? 2 : 4;
   pl.rtot_pad = 0;
@@ -151,10 +154,7 @@ SkPlan skinny_plan_of(int64_t T, const deinfer_factors_t *const *f, int n, bool 
   // workgroups fit a unit, so 258 of them on 256 units put two pairs on one unit each, and the launch
   // waits for those (traced: 15.4 us instead of 11.5 us for 86 groups x 3 ranges).  Hence the largest
   // number of k-ranges P with groups x P <= 256.
-  // (the compute units of the current device; 256, the count of the device this is written for, where
-  // no device can be asked: the host-only size query on a machine without a GPU)
-  const int cus_now = device_cus();
-  const int target = cus_now > 0 ? cus_now : 256;
+  const int target = cus > 0 ? cus : 256;
   for (int s = 0; s < 2; ++s) {
     // more than 8 ranges only for a very long k (first stage of the second MLP layer of the largest
     // models): every range keeps at least 64 k-blocks (70B shapes, k = 28672, 20 groups: 12 ranges,
@@ -192,9 +192,9 @@ SkPlan skinny_plan_of(int64_t T, const deinfer_factors_t *const *f, int n, bool 
 }
 // limit: the bytes of the caller's workspace.  One that holds the partial sums of eight ranges, not those of more, is enough
 // (a workspace sized for other calls, or fixed in a program, was before few groups took more)
-SkPlan skinny_plan(int64_t T, const deinfer_factors_t *const *f, int n, bool glu, size_t limit) {
-  const SkPlan pl = skinny_plan_of(T, f, n, glu, true);
-  return WS_HEADER + pl.t_bytes + pl.part_bytes > limit ? skinny_plan_of(T, f, n, glu, false) : pl;
+SkPlan skinny_plan(int64_t T, const deinfer_factors_t *const *f, int n, bool glu, size_t limit, int cus) {
+  const SkPlan pl = skinny_plan_of(T, f, n, glu, true, cus);
+  return WS_HEADER + pl.t_bytes + pl.part_bytes > limit ? skinny_plan_of(T, f, n, glu, false, cus) : pl;
 }
 
 // ---- k-split of the first stage of a compute-bound call
@@ -301,7 +301,7 @@ size_t workspace_need_of(int64_t T, const deinfer_factors_t *const *pairs, int n
     scratch = round_up((int64_t)tdec, 256) + round_up((int64_t)tpre, 256);
     if (T <= SKINNY_MAX_T) { // (the upward-projection-only call uses this schedule for every such T)
       for (int glu = 0; glu < 2; ++glu) {      // (the call is not known here: room for either kind)
-        const SkPlan pl = skinny_plan(T, pairs, n, glu != 0, limit);
+        const SkPlan pl = skinny_plan(T, pairs, n, glu != 0, limit, device_cus());
         const size_t sk = pl.t_bytes + pl.part_bytes;
         if (sk > scratch) scratch = sk;
       }
@@ -825,8 +825,7 @@ int deinfer_plan_decode_tile(int64_t T, const int64_t *features, int n, int64_t 
     if (!(glu && i == 1)) blocks += ceil_div(otiles[i], (int64_t)2);
   }
   const StChoice st = stream_choice(T, blocks, k_blocks, glu != 0, compute_units);
-  const bool wide = glu && !st.on && skinny_glu_one_launch(T, otiles[0], compute_units);
-  SkTile t = tile_choice(T, otiles, n, k_blocks, glu != 0, st, skinny_plan(T, pf, np, glu != 0, NO_LIMIT), wide, compute_units);
+  const SkTile t = tile_choice(T, otiles, n, k_blocks, glu != 0, st, skinny_plan(T, pf, np, glu != 0, NO_LIMIT, compute_units), compute_units);
   tile[0] = 32 * t.NB; tile[1] = 32 * t.NW; tile[2] = t.KH;
   return DEINFER_OK;
 }

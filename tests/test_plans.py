@@ -133,6 +133,40 @@ def test_second_stages_that_run_as_tiles():
     assert tile(197, 18336, 128) is None                     # 12.4 / 14.8
 
 
+def test_decode_tile_query_by_compute_units():
+    """The form that tiles are weighed against is planned for the compute units that are asked about, and the wide GLU form is
+    among the answers."""
+    def tile(features, T, k, cus):
+        return dn.deinfer_plan_decode_tile(T, [features], -(-k // 32), True, cus)
+    assert tile(2048, 17, 2072, 128) is None and tile(2048, 40, 2072, 128) is None      # against a split for 256 units: 32 x 32
+    assert tile(28672, 128, 300, 256) == (128, 128, 1)       # 224 workgroups of 128 features
+
+
+def decode_tile_call(form, kind):
+    """Return code of a call of 64 tokens with the form forced, on pointers that are not real."""
+    f = dn.Factors()
+    f.U, f.V, f.d_in, f.d_out, f.r, f.dtype, f.layout = 1 << 28, 1 << 29, 1024, 512, 256, dn.BF16, dn.LAYOUT_PACKED
+    a = ctypes.byref(f)
+    L = dn.lib()
+    dn.deinfer_set_decode_tile(form)
+    try:
+        if kind == "glu":
+            return L.deinfer_lowrank_gateup_silu(1 << 30, 64, 1024, a, a, 1 << 31, 512, 1 << 32, 1 << 30, None)
+        return L.deinfer_lowrank_linear(1 << 30, 64, 1024, a, 1 << 31, 512, 1 << 32, 1 << 30, None)
+    finally:
+        dn.deinfer_set_decode_tile(0)
+
+
+def test_decode_tile_forms_that_are_not_built_are_refused():
+    """... before anything is enqueued (without a device a launch would fail for that reason)."""
+    if torch.cuda.is_available():
+        pytest.skip("the pointers are not real")
+    linear, glu = {112, 121, 122, 131, 222, 231, 241}, {111, 121, 141, 221, 241, 441}
+    for form in sorted(linear | glu | {1, 12, 99, 100, 101, 110, 132, 212, 300, 331, 411, 999, 1112, 2 ** 31 - 1}):
+        assert decode_tile_call(form, "linear") == (dn.ERR_DEVICE if form in linear else dn.ERR_UNSUPPORTED), form
+        assert decode_tile_call(form, "glu") == (dn.ERR_DEVICE if form in glu else dn.ERR_UNSUPPORTED), form
+
+
 def test_the_static_scratch_entry_takes_a_split_that_fits():
     """First stages whose best split needs more than the static array, while a smaller one (or none) fits it: not refused for
     lack of scratch (without a device the call then fails for that reason, with one it is not made here)."""
