@@ -160,14 +160,18 @@ SkPlan skinny_plan_of(int64_t T, const deinfer_factors_t *const *f, int n, bool 
     // models): every range keeps at least 64 k-blocks (70B shapes, k = 28672, 20 groups: 12 ranges,
     // 70 -> 65 us at T = 128; the 7B shapes, k = 11008, were slower with more than 8).  Few feature groups leave the
     // device empty, and their partial sums are small: up to three groups keep 16 k-blocks per range, up to six 16 above 64
-    // tokens and 32 below (first stage alone, us: 8192 x 297 at 128 tokens 15.0 -> 13.7, 11008 x 299 18.6 -> 15.7,
-    // 14336 x 640 21.2 -> 17.4, at 32 tokens 14.8 -> 13.4; 8192 x 638 at 32 tokens would be 11.5 -> 12.0 with 16, ten
-    // groups, 8192 x 1200, at 32 tokens 12.1 -> 12.5)
+    // tokens and 32 below, where that gives at least twelve ranges.  First stage alone with the weights from HBM, 1313
+    // random shapes (9 .. 128 tokens, k = 2560 .. 30000, up to twelve groups): the 675 that take more ranges are on average
+    // 17 % faster than with 64 k-blocks per range, none more than 2.5 % slower; with nine ranges 5 % slower (4904 x 19 at 32
+    // tokens 9.2 -> 10.0 us: rounded up to whole stages eight of them cover the k range), ten and eleven up to 5 % either way
+    // (8192 x 297 at 128 tokens 15.0 -> 13.7 us, 11008 x 299 18.6 -> 15.7, 14336 x 640 21.2 -> 17.4, at 32 tokens
+    // 14.8 -> 13.4)
     int cap = 8;
     const int g4 = groups_of(s, 4);
     if (s == 0) {
       const int keep = !more ? 64 : g4 <= 3 || (g4 <= 6 && T > 64) ? 16 : g4 <= 6 ? 32 : 64;
-      const int by_k = (int)(ceil_div(f[0]->d_in, 32) / keep);
+      int by_k = (int)(ceil_div(f[0]->d_in, 32) / keep);
+      if (keep < 64 && by_k < 12) by_k = (int)(ceil_div(f[0]->d_in, 32) / 64);
       cap = by_k > SK_MAX_PARTS ? SK_MAX_PARTS : by_k > 8 ? by_k : 8;
     }
     const bool direct = s == 1 && !glu && (g4 > target / 2 || g4 >= SK_DIRECT_MIN_GROUPS);

@@ -180,6 +180,36 @@ def test_the_static_scratch_entry_takes_a_split_that_fits():
         assert rc == dn.ERR_DEVICE, dn.last_error()
 
 
+def few_group_ranges(T, d_in, ranks):
+    """k-ranges of the first stage of a T <= 128 call on packed pairs of few features, from the workspace it asks for: the
+    partial sums against those of a short k, which takes eight."""
+    def part(k):
+        fs = []
+        for r in ranks:
+            f = dn.Factors()
+            f.U, f.V, f.d_in, f.d_out, f.r, f.dtype, f.layout = 1 << 28, 1 << 29, k, 16, r, dn.BF16, dn.LAYOUT_PACKED
+            fs.append(types.SimpleNamespace(desc=f))
+        rows = 32 if T <= 32 else 64 if T <= 64 else 128
+        return dn.deinfer_workspace_bytes(T, fs) - 256 - -(-rows * sum(-(-r // 32) * 32 for r in ranks) * 2 // 256) * 256
+    assert 8 * part(d_in) % part(1024) == 0
+    return 8 * part(d_in) // part(1024)
+
+
+@pytest.mark.skipif(torch.cuda.is_available(), reason="sized for the 256 compute units that a machine without a device assumes")
+def test_k_ranges_of_first_stages_of_few_feature_groups():
+    # timed with 64, 48, 32, 24, 16 and 12 k-blocks per range (us: eight ranges / as many as are taken)
+    assert few_group_ranges(128, 8192, (297,)) == 16            # 15.0 / 13.7
+    assert few_group_ranges(128, 11008, (299,)) == 16           # 18.6 / 15.7
+    assert few_group_ranges(128, 14336, (640,)) == 16           # 21.2 / 17.4
+    assert few_group_ranges(32, 14336, (640,)) == 14            # 14.8 / 13.4
+    assert few_group_ranges(32, 8192, (638,)) == 8              # 11.5, 12.0 in 16
+    # fewer than twelve: (9 ranges) 9.2, 10.0; 10.4, 11.2; (11) 9.1, 9.4
+    assert few_group_ranges(32, 4904, (19,)) == 8
+    assert few_group_ranges(33, 4960, (22, 22)) == 8
+    assert few_group_ranges(9, 5912, (140,)) == 8
+    assert few_group_ranges(128, 6144, (40,)) == 12 and few_group_ranges(128, 6112, (40,)) == 8
+
+
 @pytest.mark.parametrize("T", [32, 64, 128])
 def test_a_workspace_of_eight_ranges_is_taken(T):
     """Few feature groups and a long k: more than eight k-ranges where the workspace holds their sums, eight in a smaller one
