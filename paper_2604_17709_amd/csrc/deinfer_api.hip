@@ -829,7 +829,7 @@ int deinfer_plan_decode_tile(int64_t T, const int64_t *features, int n, int64_t 
     if (!(glu && i == 1)) blocks += ceil_div(otiles[i], (int64_t)2);
   }
   const StChoice st = stream_choice(T, blocks, k_blocks, glu != 0, compute_units);
-  const SkTile t = tile_choice(T, otiles, n, k_blocks, glu != 0, st, skinny_plan(T, pf, np, glu != 0, NO_LIMIT, compute_units), compute_units);
+  const SkTile t = tile_choice(T, otiles, n, k_blocks, glu != 0, st, skinny_plan(T, pf, np, glu != 0, NO_LIMIT, compute_units), false, compute_units);
   tile[0] = 32 * t.NB; tile[1] = 32 * t.NW; tile[2] = t.KH;
   return DEINFER_OK;
 }
