@@ -161,7 +161,10 @@ def _stream(stream) -> Optional[int]:
     import torch
     if stream is None:
         if torch.cuda.is_initialized():      # the handle of torch.cuda.current_stream(), without making that object (4 us a call)
-            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()) or None
+            try:
+                return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()) or None
+            except AttributeError:           # (names of torch's own: a torch may lack them)
+                pass
         stream = torch.cuda.current_stream()
     h = int(stream.cuda_stream)
     return h if h else None

@@ -286,6 +286,19 @@ def test_static_scratch_entry_point_validates_on_the_host():
     assert "#define DEINFER_STATIC_SCRATCH_BYTES (32u << 20)" in header and dn.STATIC_SCRATCH_BYTES == 32 << 20
 
 
+@pytest.mark.parametrize("missing", ["_cuda_getCurrentRawStream", "_cuda_getDevice"])
+def test_current_stream_without_the_raw_query(monkeypatch, missing):
+    """The launch stream of a call that names none, on a torch that lacks one of its own names for the raw handle."""
+    import torch
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 0x1000 + device, raising=False)
+    monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 3, raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: type("S", (), {"cuda_stream": 0x2000}))
+    assert dn._stream(None) == 0x1003
+    monkeypatch.delattr(torch._C, missing)
+    assert dn._stream(None) == 0x2000
+
+
 def test_missing_library_fails_loudly(monkeypatch):
     monkeypatch.setattr(dn, "_lib", None)
     monkeypatch.setattr(dn, "LIB_PATH", os.path.join(ROOT, "does_not_exist.so"))
