@@ -33,6 +33,10 @@ def token_tile(request, dn):
     dn.deinfer_set_prefill_feature_tile(0)
 
 
+# for tests of calls of at most 128 tokens: once, not once for each tile of the T > 128 kernel
+one_token_tile = pytest.mark.parametrize("token_tile", [(0, 0)], indirect=True, ids=["tiles-auto"])
+
+
 def ws_for(dn, T, pairs):
     return dn.Workspace(dn.deinfer_workspace_bytes(T, pairs))
 
@@ -470,7 +474,7 @@ def test_keys_rebuilt_from_the_low_rank_cache(dn, T):
     assert max_err(to_host(k2), to_host(k).astype(np.float64)) <= 2.0 ** -7    # at most an output rounding apart
 
 
-# (d_in, r, d_out), with the form of the second stage on 256 compute units (tests/test_plans.py)
+# (d_in, r, d_out), with the form of the second stage on 256 compute units where no tiles are taken (tests/test_plans.py)
 DECODE_STAGE_ROWS = [
     (264, 37, 40),          # one launch per stage, a few workgroups
     (1000, 1021, 200),      # ... k ends inside the last short k-block range
@@ -478,16 +482,26 @@ DECODE_STAGE_ROWS = [
     (72, 250, 8200),        # 257 blocks: more than the compute units, left to the split
     (72, 250, 8100),        # 254 blocks: two token blocks per workgroup, also for the GLU call
     (4200, 1037, 136),      # both stages split over k, with the reduce launch
-    (264, 1500, 3100),      # 97 blocks, long k: one token block per workgroup up to 64 tokens, then two
-    (264, 1900, 4300),      # 135 blocks, long k: two up to 64 tokens, then the split
+    (264, 1500, 3100),      # 97 blocks, long k: the split, one token block per workgroup from 33 tokens, two from 65
+    (264, 1900, 4300),      # 135 blocks, long k: one, from 33 tokens two, from 65 the split
 ]
 
 
+@pytest.fixture
+def decode_tile(request, dn):
+    dn.deinfer_set_decode_tile(request.param)
+    yield request.param
+    dn.deinfer_set_decode_tile(0)
+
+
+@one_token_tile
+@pytest.mark.parametrize("decode_tile", [0, -1], indirect=True, ids=["chosen", "no-tiles"])
 @pytest.mark.parametrize("T", [9, 17, 33, 64, 65, 97, 128])
 @pytest.mark.parametrize("d_in,r,d_out", DECODE_STAGE_ROWS)
-def test_decode_stages_by_token_blocks(dn, T, d_in, r, d_out):
+def test_decode_stages_by_token_blocks(dn, decode_tile, T, d_in, r, d_out):
     """Both sides of the choice between one launch of token blocks and the k-split, in both stages, with the
-    rank-space output, the GLU form and the upward projection alone on rows that end in NaN."""
+    rank-space output, the GLU form and the upward projection alone on rows that end in NaN; the second stages also where
+    they would run as tiles."""
     import torch
     x, U, V = gen(80, T, d_in, r, d_out, "bf16")
     p, keep = pair(dn, U, V, packed=True)
@@ -670,12 +684,16 @@ def test_stages_as_separate_calls(dn, kind, T):
 
 
 # ------------------------------------------------------------------ second stages as tiles over the whole k range
+LINEAR_TILES, GLU_TILES = (112, 121, 122, 131, 222, 231, 241), (111, 121, 141, 221, 241, 441)
+
+
+@one_token_tile
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("T", [9, 32, 33, 64, 65, 128])
 def test_second_stage_as_tiles(dn, dtype, T):
     """Every tile that is built, forced: three products of different ranks and ragged widths in one launch, bias and
     activation, GLU with ranks of different length, and the staged calls on rank-space rows embedded in NaN (ranks that are
-    no multiple of 8, the last chunk in the first or the second half of the k range)."""
+    no multiple of 8; the last chunk in the second half of the k range, or in the first with the second half empty)."""
     import torch
     d_in = 136
     x = si.make(61, 1, (T, d_in), 1.0, dtype)
@@ -698,13 +716,13 @@ def test_second_stage_as_tiles(dn, dtype, T):
     ref_qkv = oracle.lowrank_qkv(x.values, *host[0], *host[1], *host[2])
     ref_act = np.maximum(oracle.lowrank_linear(x.values, *host[0]) + bias.values, 0.0)
     ref_glu = oracle.lowrank_gateup_silu(x.values, *host[0], *host[2])
-    ref_up = [oracle.up_projection(rows_host[i], host[i][1]) for i in (0, 2)]
+    ref_up = [oracle.up_projection(t, h[1]) for t, h in zip(rows_host, host)]
     ref_upglu = oracle.up_glu_silu(rows_host[0], host[0][1], rows_host[2], host[2][1])
 
     def room():
         return torch.full((T, 1240), 9.0, dtype=xd.dtype, device="cuda")          # pitch > width: nothing may be written past d_out
     try:
-        for form in (112, 121, 122, 131, 222, 231, 241):
+        for form in LINEAR_TILES:
             dn.deinfer_set_decode_tile(form)
             out = [room(), room(), room()]
             dn.deinfer_lowrank_qkv(xd, *F, ws, out=tuple(o[:, :f.d_out] for o, f in zip(out, F)))
@@ -712,9 +730,9 @@ def test_second_stage_as_tiles(dn, dtype, T):
                 assert max_err(to_host(o[:, :f.d_out]), ref) <= TOL[dtype], form
                 assert float((o[:, f.d_out:].float() - 9.0).abs().max()) == 0.0
             assert max_err(to_host(dn.deinfer_lowrank_linear_act(xd, F[0], ws, bias=bd, act=dn.ACT_RELU)), ref_act) <= TOL[dtype], form
-            for i, ref in zip((0, 2), ref_up):
-                assert max_err(to_host(dn.deinfer_lowrank_up(rows[i], F[i], ws)), ref) <= TOL[dtype], form
-        for form in (111, 121, 141, 221, 241, 441):
+            for t, f, ref in zip(rows, F, ref_up):
+                assert max_err(to_host(dn.deinfer_lowrank_up(t, f, ws)), ref) <= TOL[dtype], form
+        for form in GLU_TILES:
             dn.deinfer_set_decode_tile(form)
             h = room()
             dn.deinfer_lowrank_gateup_silu(xd, F[0], F[2], ws, out=h[:, :1234])
@@ -745,6 +763,46 @@ def test_second_set_of_rank_space_rows_with_a_very_large_pitch(dn, T, pitch):
     assert max_err(to_host(h), oracle.up_glu_silu(rows[0].values, V[0].values, rows[1].values, V[1].values)) <= TOL["bf16"]
 
 
+@one_token_tile
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("T,r_gate,r_up", [(33, 1301, 2092), (64, 2600, 1093), (128, 2092, 1301)])
+def test_second_stage_as_tiles_of_a_long_k_range(dn, dtype, T, r_gate, r_up):
+    """More stages than a wavefront's four slabs (41, 66 or 82 k-blocks: 6 to 11 stages in each half of the range), every tile
+    forced, on rank-space rows that end in NaN and inside a whole call."""
+    import torch
+    d_in, d_out = 72, 200
+    x = si.make(62, 1, (T, d_in), 1.0, dtype)
+    F, host, rows, rows_host = [], [], [], []
+    for i, r in enumerate((r_gate, r_up)):
+        U = si.make(62, 10 + 2 * i, (d_in, r), 1.0 / np.sqrt(d_in), dtype)
+        V = si.make(62, 11 + 2 * i, (r, d_out), 1.0 / np.sqrt(r), dtype)
+        F.append(pair(dn, U, V, packed=True)[0])
+        host.append((U.values, V.values))
+        t = si.make(62, 20 + i, (T, r), 1.0, dtype)
+        buf = torch.full((T, (r + 7) // 8 * 8 + 8), float("nan"), dtype=torch.float16 if dtype == "f16" else torch.bfloat16, device="cuda")
+        buf[:, :r] = to_dev(t)
+        rows.append(buf[:, :r])
+        rows_host.append(t.values)
+    xd, ws = to_dev(x), ws_for(dn, T, F)
+    ref = [oracle.lowrank_linear(x.values, *h) for h in host]
+    ref_up = [oracle.up_projection(t, h[1]) for t, h in zip(rows_host, host)]
+    ref_glu = oracle.lowrank_gateup_silu(x.values, *host[0], *host[1])
+    ref_upglu = oracle.up_glu_silu(rows_host[0], host[0][1], rows_host[1], host[1][1])
+    try:
+        for form in LINEAR_TILES:
+            dn.deinfer_set_decode_tile(form)
+            for i in (0, 1):
+                assert max_err(to_host(dn.deinfer_lowrank_linear(xd, F[i], ws)), ref[i]) <= TOL[dtype], form
+                assert max_err(to_host(dn.deinfer_lowrank_up(rows[i], F[i], ws)), ref_up[i]) <= TOL[dtype], form
+        for form in GLU_TILES:
+            dn.deinfer_set_decode_tile(form)
+            assert max_err(to_host(dn.deinfer_lowrank_gateup_silu(xd, *F, ws)), ref_glu) <= TOL[dtype], form
+            assert max_err(to_host(dn.deinfer_lowrank_up_glu_silu(*rows, *F, ws)), ref_upglu) <= TOL[dtype], form
+    finally:
+        dn.deinfer_set_decode_tile(0)
+
+
+@one_token_tile
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("r", [96, 819, 832, 872])
 def test_infinite_rank_space_values_in_tiles(dn, dtype, r):
@@ -768,7 +826,7 @@ def test_infinite_rank_space_values_in_tiles(dn, dtype, r):
     ref = oracle.up_projection(to_host(t)[good], to_host(V[0]))
     ref_glu = oracle.up_glu_silu(to_host(t)[good], to_host(V[0]), to_host(t)[good], to_host(V[1]))
     try:
-        for glu, forms in ((False, (112, 121, 122, 131, 222, 231, 241)), (True, (111, 121, 141, 221, 241, 441))):
+        for glu, forms in ((False, LINEAR_TILES), (True, GLU_TILES)):
             for form in forms:
                 dn.deinfer_set_decode_tile(form)
                 y = dn.deinfer_lowrank_up_glu_silu(t, t, F[0], F[1], ws) if glu else dn.deinfer_lowrank_up(t, F[0], ws)
@@ -778,11 +836,19 @@ def test_infinite_rank_space_values_in_tiles(dn, dtype, r):
         dn.deinfer_set_decode_tile(0)
 
 
-@pytest.mark.parametrize("T,ranks", [(17, (40,)), (64, (130, 46, 46)), (128, (297,)), (128, (400, 260)), (100, (700,))])
-def test_first_stages_of_few_feature_groups(dn, T, ranks):
+# (T, d_in, ranks): packed first stages that take more than eight k-ranges on 256 compute units (tests/test_plans.py)
+FEW_GROUP_ROWS = [
+    (17, 8232, (40,)), (128, 8232, (297,)),                        # up to three groups: 16 k-blocks per range
+    (100, 8232, (700,)), (128, 8232, (330, 260)),                  # up to six, above 64 tokens: 16
+    (32, 14376, (640,)), (64, 14376, (640,)), (64, 14376, (130, 200, 130)),      # ... below: 32
+]
+
+
+@one_token_tile
+@pytest.mark.parametrize("T,d_in,ranks", FEW_GROUP_ROWS + [(128, 8232, (400, 260))])
+def test_first_stages_of_few_feature_groups(dn, T, d_in, ranks):
     """Long k and few features: more than eight k-ranges of 16 or 32 k-blocks (the last one shorter), summed in two rounds
-    of the adding launch."""
-    d_in = 8192 + 40
+    of the adding launch; and seven groups, which take eight."""
     x = si.make(71, 1, (T, d_in), 1.0, "bf16")
     F, U = [], []
     for i, r in enumerate(ranks):
@@ -794,6 +860,7 @@ def test_first_stages_of_few_feature_groups(dn, T, ranks):
     ws.check()
 
 
+@one_token_tile
 @pytest.mark.parametrize("T", [32, 64, 128])
 def test_first_stage_of_few_feature_groups_in_a_smaller_workspace(dn, T):
     import torch

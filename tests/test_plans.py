@@ -113,9 +113,16 @@ def test_form_of_measured_decode_stages():
 
 
 def test_every_form_of_a_decode_stage_is_taken_by_the_rows_of_its_test():
+    """... without tiles, and (where the stage chooses) by a row that is not left to tiles."""
     from test_gpu_parity import DECODE_STAGE_ROWS
-    forms = {(glu, stage(r, d_out, T, glu), T > 64) for T in (9, 17, 33, 64, 65, 97, 128) for _, r, d_out in DECODE_STAGE_ROWS for glu in (False, True)}
-    assert forms >= {(g, f, late) for g in (False, True) for f in (0, 1, 2) for late in (False, True)}
+    forms, chosen = set(), set()
+    for T, (_, r, d_out), glu in itertools.product((9, 17, 33, 64, 65, 97, 128), DECODE_STAGE_ROWS, (False, True)):
+        form = (glu, stage(r, d_out, T, glu), T > 64)
+        forms.add(form)
+        if dn.deinfer_plan_decode_tile(T, [d_out], -(-r // 32), glu, CUS) is None:
+            chosen.add(form)
+    every = {(g, f, late) for g in (False, True) for f in (0, 1, 2) for late in (False, True)}
+    assert forms >= every and chosen >= every, every - chosen
 
 
 def test_second_stages_that_run_as_tiles():
@@ -207,6 +214,10 @@ def few_group_ranges(T, d_in, ranks):
 
 @pytest.mark.skipif(torch.cuda.is_available(), reason="sized for the 256 compute units that a machine without a device assumes")
 def test_k_ranges_of_first_stages_of_few_feature_groups():
+    from test_gpu_parity import FEW_GROUP_ROWS
+    for T, d_in, ranks in FEW_GROUP_ROWS:
+        assert few_group_ranges(T, d_in, ranks) > 8, (T, d_in, ranks)
+    assert few_group_ranges(128, 8232, (400, 260)) == 8         # seven groups
     # timed with 64, 48, 32, 24, 16 and 12 k-blocks per range (us: eight ranges / as many as are taken)
     assert few_group_ranges(128, 8192, (297,)) == 16            # 15.0 / 13.7
     assert few_group_ranges(128, 11008, (299,)) == 16           # 18.6 / 15.7
