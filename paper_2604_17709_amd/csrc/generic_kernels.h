@@ -45,9 +45,12 @@ template <typename TA, typename TB> struct RawOperands {
   int K;
 };
 
-// register buffers of k-steps in flight: about 16 KiB per wavefront for the large tiles (the loads of a step
-// are requested 2 x 2000 matrix cycles ahead), more steps where a step is small
-constexpr int raw_depth(int mb, int nv) { return mb * nv >= 16 ? 4 : mb * nv >= 8 ? 5 : 7; }
+// Register buffers of k-steps: one is multiplied while the next D - 1 are on their way.  A step of a 64 x 64 tile is 8 KiB
+// per wavefront in fp32 and 2000 matrix cycles, so its loads are requested 4000 cycles ahead; smaller steps, more of them.
+// One buffer more (4, 5, 7) is 1 to 5 % slower, by tile, on average over 3000 random products, the most where the k range is
+// a few steps, and no faster on long ones (first stages in fp32, us: 201 x 4096 x 1638 47.6, 47.5; 16 x 700 x 300
+// 6.26, 6.57; 201 x 1638 x 4096 35.5, 35.2).
+constexpr int raw_depth(int mb, int nv) { return mb * nv >= 16 ? 3 : mb * nv >= 8 ? 4 : 6; }
 
 // acc[i][j] += A[m0 + 16 i .., :] . B[:, column block j of n0 ..], this wavefront's part of the k range.
 // EDGE: the tile reaches beyond column N - 1 (columns clamped; what they give is not stored).
