@@ -134,6 +134,8 @@ def test_second_stages_that_run_as_tiles():
     assert tile(512, 10240, 64) in ((32, 96, 1), (64, 128, 1))  # 13.0 / 7.6, 7.8
     assert tile(1640, 8192, 64) in ((32, 64, 1), (32, 64, 2))   # 15.7 / 11.5, 11.2
     assert tile(1640, 8192, 128, True) == (64, 64, 1)        # 29.4 / 20.2
+    assert tile(2392, 11008, 8, True) == (32, 64, 1)         # 22.2 / 21.5
+    assert tile(3824, 11344, 32, True) is None               # 32.5 / 34.2
     assert tile(3440, 10240, 64) is None                     # 21.9 / 22.2
     assert tile(3440, 2048, 32) is None                      # 9.4 / 11.8
     assert tile(3440, 5504, 64, True) is None                # 22.3 / 27.7
