@@ -481,12 +481,14 @@ void launch_raw(const RawCall<TA, TB, TC, DUAL> &c, hipStream_t s) {
 // Tile of a product: the one with the smallest estimate  rounds of workgroups x (k x time per k + epilogue), over
 // the compute units.  Times in units of one k of the 16 x 16 tile, for fp32 and for 16-bit B rows (which a 64 x 32
 // tile reads in 4-byte pieces), fitted to all six tiles timed on 1107 products (M = 1 .. 2048, N = 63 .. 4096,
-// k = 64 .. 4096, B rotated over more than 256 MB).  The choice is on average 0.8 % behind the best of the six and at
-// most 23 % (fp32 512 x 1024 x 4096: 64 x 32 53.6 us, 32 x 64 43.4).  201 x 1638 x 4096 in fp32: 64 x 32 49.2 us,
-// 64 x 64 64.6, 16 x 32 64.5; 201 x 4096 x 1638: 64 x 64 33.9 us, 32 x 64 39.5; in bf16 201 x 1638 x 1638: 16 x 32 22.5,
-// 64 x 32 38.0.
+// k = 64 .. 4096, B rotated over more than 256 MB) before the rows of A crossed lanes.  Over 4500 other products (M = 1 .. 2048,
+// N = 63 .. 12000, k = 64 .. 8192; whole 16-byte pieces of B's rows or not, two products or one) the choice is on average
+// 2.6 % behind the best of the six and at most 77 %, 2.9 % with the kernel before; constants fitted anew gained 0.7 % in fp32
+// and 0.9 % in 16 bits on average and lost up to 40 % on single products (M x N x k = 1876 x 188 x 4132, 64 x 32 46.1 us, 32 x 64
+// 66.0).  201 x 1638 x 4096 in fp32: 64 x 32 46.9 us, 32 x 32 52.3, 16 x 32 63.4; 201 x 4096 x 1638: 64 x 64 33.8 us, 32 x 64
+// 35.0; in bf16 201 x 1638 x 1638: 32 x 32 23.6, 16 x 32 24.8, 64 x 32 33.8.
 // Tiles of 64 columns read four elements of a B row at once and need those rows aligned to the four (a row
-// pitch of 819 fp32 elements: 77 us for 512 x 819 x 4096 as 32 x 64 tiles against 49 as 64 x 32); with two products
+// pitch of 819 fp32 elements: 77 us for 512 x 819 x 4096 as 32 x 64 tiles against 46 as 64 x 32); with two products
 // (dual) their sums would not leave room for them.
 struct RawTile { int mb, nv; double per_k, fixed; };
 constexpr RawTile RAW_TILES[2][6] = {
@@ -501,9 +503,11 @@ RawChoice raw_choice(int64_t M, int64_t N, double k, bool fp32, bool rows4, bool
     const double cost = (double)ceil_div(ceil_div(M, 16 * t.mb) * ceil_div(N, 16 * t.nv), (int64_t)cus) * (t.per_k * k + t.fixed);
     if (best.mb == 0 || cost < best_cost) { best.mb = t.mb; best.nv = t.nv; best_cost = cost; }
   }
-  // few tiles and a long k: 16 wavefronts share the k range of a tile instead of four (k = 4096, one row, up to 64
-  // tiles: fp32 5 to 10 % faster, bf16 20 to 30; 16 rows: fp32 within 4 %, bf16 6 to 15 % faster; k = 1638, 16 rows:
-  // fp32 26 to 34 % slower)
+  // few tiles and a long k: 16 wavefronts share the k range of a tile instead of four.  16-bit first stages gain (67 products
+  // of k >= 4096: 14 % on average; 16 x 4096 x 300 21.0 -> 19.2 us, below 4096 8 %); with fp32 rows of A, i.e. fp32 pairs and
+  // 16-bit second stages, they lose 6 to 7 % on average (60 and 68 products; 9 % from k = 2048 to 4096), where one row of A and
+  // 64 columns take 12.5 us either way: the line is a compromise of the two, from before the rows of A crossed lanes (fp32 5 %
+  // slower, 16-bit second stages even)
   if (best.mb == 1 && best.nv == 1 && 4 * ceil_div(M, 16) * ceil_div(N, 16) <= cus && k >= 4096) best.nw = 16;
   return best;
 }
