@@ -136,6 +136,8 @@ def test_second_stages_that_run_as_tiles():
     assert tile(1640, 8192, 128, True) == (64, 64, 1)        # 29.4 / 20.2
     assert tile(2392, 11008, 8, True) == (32, 64, 1)         # 22.2 / 21.5
     assert tile(3824, 11344, 32, True) is None               # 32.5 / 34.2
+    assert tile(1968, 8748, 13) == (32, 64, 2)               # 13.0 / 11.6
+    assert tile(2368, 11604, 2) == (32, 64, 2)               # 15.2 / 13.4
     assert tile(3440, 10240, 64) is None                     # 21.9 / 22.2
     assert tile(3440, 2048, 32) is None                      # 9.4 / 11.8
     assert tile(3440, 5504, 64, True) is None                # 22.3 / 27.7
