@@ -845,10 +845,10 @@ FEW_GROUP_ROWS = [
 
 
 @one_token_tile
-@pytest.mark.parametrize("T,d_in,ranks", FEW_GROUP_ROWS + [(128, 8232, (400, 260))])
+@pytest.mark.parametrize("T,d_in,ranks", FEW_GROUP_ROWS + [(64, 8232, (130, 46, 46)), (128, 8232, (400, 260))])
 def test_first_stages_of_few_feature_groups(dn, T, d_in, ranks):
     """Long k and few features: more than eight k-ranges of 16 or 32 k-blocks (the last one shorter), summed in two rounds
-    of the adding launch; and seven groups, which take eight."""
+    of the adding launch; and rows that take eight (too few k-blocks, seven groups)."""
     x = si.make(71, 1, (T, d_in), 1.0, "bf16")
     F, U = [], []
     for i, r in enumerate(ranks):

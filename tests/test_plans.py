@@ -132,7 +132,7 @@ def test_second_stages_that_run_as_tiles():
     assert tile(1640, 8192, 128) == (64, 64, 2)              # 21.5 / 14.4
     assert tile(1640, [8192, 1024, 1024], 128) == (64, 96, 1)   # 23.1 / 15.7
     assert tile(512, 10240, 64) in ((32, 96, 1), (64, 128, 1))  # 13.0 / 7.6, 7.8
-    assert tile(1640, 8192, 64) in ((32, 64, 1), (32, 64, 2))   # 15.7 / 11.5, 11.2
+    assert tile(1640, 8192, 64) == (32, 64, 2)               # 15.4 / 11.8
     assert tile(1640, 8192, 128, True) == (64, 64, 1)        # 29.4 / 20.2
     assert tile(2392, 11008, 8, True) == (32, 64, 1)         # 22.2 / 21.5
     assert tile(3824, 11344, 32, True) is None               # 32.5 / 34.2
